@@ -37,14 +37,19 @@ __device__ __forceinline__ int lane_id()
 }
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
 
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+
 constexpr int kDppWaveShl1 = 0x130;
 constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
 constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
 
+// (v_alignbyte_b32 takes the low two bits of its shift operand, so a byte
+// position goes in as it is)
 __device__ __forceinline__ uint32_t lds_le32(const uint32_t *b32, int pos)
 {
     const uint32_t w0 = b32[pos >> 2], w1 = b32[(pos >> 2) + 1];
-    return __builtin_amdgcn_alignbyte(w1, w0, (uint32_t)(pos & 3));
+    return __builtin_amdgcn_alignbyte(w1, w0, (uint32_t)pos);
 }
 
 // ---- stage the block into LDS as bit planes -------------------------------
@@ -305,13 +310,18 @@ __device__ __forceinline__ int wave_excl_scan(int x, int &total)
     return s - x;
 }
 
-// lds_le32 for a position as far as 3 bytes before the block: the bytes
-// before it come out undefined.
-__device__ __forceinline__ uint32_t lds_le32_head(const uint32_t *b32, int pos)
+// Inclusive running maximum over the wave's lanes (x >= 0), as
+// wave_excl_scan.
+__device__ __forceinline__ int wave_max_scan(int x)
 {
-    const int wi = pos >> 2;
-    const uint32_t w0 = b32[wi < 0 ? 0 : wi], w1 = b32[wi + 1];
-    return __builtin_amdgcn_alignbyte(w1, w0, (uint32_t)(pos & 3));
+    const auto up = [](int a, int b) { return a > b ? a : b; };
+    x = up(x, __builtin_amdgcn_update_dpp(0, x, kDppRowShr1, 0xF, 0xF, true));
+    x = up(x, __builtin_amdgcn_update_dpp(0, x, kDppRowShr2, 0xF, 0xF, true));
+    x = up(x, __builtin_amdgcn_update_dpp(0, x, kDppRowShr4, 0xF, 0xF, true));
+    x = up(x, __builtin_amdgcn_update_dpp(0, x, kDppRowShr8, 0xF, 0xF, true));
+    x = up(x, __builtin_amdgcn_update_dpp(0, x, kDppRowBcast15, 0xA, 0xF, false));
+    x = up(x, __builtin_amdgcn_update_dpp(0, x, kDppRowBcast31, 0xC, 0xF, false));
+    return x;
 }
 
 // Write the ns (<= 64) sequences that lanes 0 .. ns-1 hold (lane j: the
@@ -319,9 +329,8 @@ __device__ __forceinline__ uint32_t lds_le32_head(const uint32_t *b32, int pos)
 // distance off; ml == 0 marks the block's last sequence, literals only) from
 // byte op of the 16-byte aligned slot dst; returns the byte after them.
 // Each lane writes its own token, offset and length bytes; then the wave
-// copies the literal runs, 16 output bytes per lane per step: whole dwords
-// where a run covers them, single bytes at a run's ends.  The block must be
-// readable 4 bytes past every run.
+// copies the literal runs, 16 output bytes per lane per step.  The block
+// must be readable 20 bytes past every run.
 __device__ __forceinline__ int emit_sequences(uint8_t *__restrict__ dst, int op, const uint32_t *b32,
                                               int ns, int lit, int ll, int off, int ml)
 {
@@ -342,7 +351,7 @@ __device__ __forceinline__ int emit_sequences(uint8_t *__restrict__ dst, int op,
     const int tpos = start + hsz + ll;
     const int fmax = act ? (hsz > tsz ? hsz : tsz) : 0;
     constexpr int kShort = 4; // field bytes each lane writes itself
-    for (int k = 0; k < kShort && __ballot(k < fmax) != 0; ++k) {
+    for (int k = 0; k < kShort && ballot(k < fmax) != 0; ++k) {
         if (act && k < hsz) dst[start + k] = (uint8_t)(k == 0 ? tok : (k < lext ? 255u : lrem));
         if (act && k < tsz)
             dst[tpos + k] = (uint8_t)(k == 0 ? (uint32_t)off & 255u
@@ -350,49 +359,73 @@ __device__ __forceinline__ int emit_sequences(uint8_t *__restrict__ dst, int op,
     }
     // the rest of a long length field (a run of 255s, then the remainder):
     // the wave writes one such sequence at a time
-    for (uint64_t longs = __ballot(fmax > kShort); longs; longs &= longs - 1) {
+    for (uint64_t longs = ballot(fmax > kShort); longs; longs &= longs - 1) {
         const int j = __builtin_ctzll(longs);
         const int st_j = __builtin_amdgcn_readlane(start, j), h_j = __builtin_amdgcn_readlane(hsz, j);
         const int tp_j = __builtin_amdgcn_readlane(tpos, j), t_j = __builtin_amdgcn_readlane(tsz, j);
         const uint32_t lr_j = (uint32_t)__builtin_amdgcn_readlane((int)lrem, j);
         const uint32_t mr_j = (uint32_t)__builtin_amdgcn_readlane((int)mrem, j);
+#pragma unroll 1
         for (int k = kShort + lane; k < h_j; k += kWave) dst[st_j + k] = (uint8_t)(k < h_j - 1 ? 255u : lr_j);
+#pragma unroll 1
         for (int k = kShort + lane; k < t_j; k += kWave) dst[tp_j + k] = (uint8_t)(k < t_j - 1 ? 255u : mr_j);
     }
 
-    // literal runs: task t of the wave is the 16 output bytes (ls_j / 16) +
-    // t - first_j of the sequence j with first_j <= t < first_{j+1}
-    const int ls = start + hsz;
-    const int nd = act && ll > 0 ? ((ls + ll - 1) >> 4) - (ls >> 4) + 1 : 0;
+    // literal runs: the up to 3 bytes before a run's first whole output
+    // dword and after its last one, by the sequence's own lane
+    const int ls = start + hsz, le = ls + ll;
+    const int w0 = (ls + 3) >> 2, w1 = le >> 2; // its whole dwords: [w0, w1)
+    if (act && ll > 0) {
+        const int h1 = 4 * w0 < le ? 4 * w0 : le;
+        const uint32_t hv = lds_le32(b32, lit);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (ls + i < h1) dst[ls + i] = (uint8_t)(hv >> (8 * i));
+        const int t0 = w1 < w0 ? le : 4 * w1; // (w1 < w0: all inside one dword)
+        const uint32_t tv = lds_le32(b32, lit + (t0 - ls));
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (t0 + i < le) dst[t0 + i] = (uint8_t)(tv >> (8 * i));
+    }
+
+    // whole dwords: task t of the wave is the part of run j inside the 16
+    // output bytes (w0_j / 4) + t - first_j, for the sequence j with first_j
+    // <= t < first_{j+1}
+    const int nd = act && w1 > w0 ? ((w1 - 1) >> 2) - (w0 >> 2) + 1 : 0;
     int ndt;
     const int first = wave_excl_scan(nd, ndt);
     uint32_t *dst32 = reinterpret_cast<uint32_t *>(dst);
-    for (int t0 = 0; t0 < ndt; t0 += kWave) {
-        const int t = t0 + lane;
-        int j = 0; // the last sequence whose first task is <= t
+    const int unit0 = (w0 >> 2) - first; // the run's unit of task t: t + unit0
+    const int delta = lit - ls;          // input byte - output byte
+    int jc = 0; // the last sequence of the steps so far
+    constexpr int kTasks = kWave - 1; // per step: lane 63 takes what no lane wants
+    for (int t0 = 0; t0 < ndt; t0 += kTasks) {
+        // the sequences whose tasks start in this step send their index to
+        // their first task's lane (lanes nobody sends to get 0), and a
+        // running maximum carries it over the tasks after it
+        const int at = nd > 0 && first >= t0 ? first - t0 : kTasks;
+        int j = __builtin_amdgcn_ds_permute(4 * (at < kTasks ? at : kTasks), lane);
+        j = lane < kTasks ? j : 0;
+        j = wave_max_scan(j > jc ? j : jc);
+        jc = __builtin_amdgcn_readlane(j, kTasks - 1);
+        const int u = t0 + lane + __shfl(unit0, j);
+        const int d_j = __shfl(delta, j), w0_j = __shfl(w0, j), w1_j = __shfl(w1, j);
+        if (lane < kTasks && t0 + lane < ndt) {
+            // the dwords [v, e) of the unit, all but a run's first and last
+            // unit whole ones
+            const int v = 4 * u > w0_j ? 4 * u : w0_j, e = 4 * u + 4 < w1_j ? 4 * u + 4 : w1_j;
+            const int sp = 4 * v + d_j;
+            const uint32_t *sw = b32 + (sp >> 2);
+            uint32_t x[4];
 #pragma unroll
-        for (int st = kWave / 2; st >= 1; st >>= 1) {
-            const int fj = __shfl(first, j + st);
-            j = j + st < ns && fj <= t ? j + st : j;
-        }
-        const int ls_j = __shfl(ls, j), ll_j = __shfl(ll, j);
-        const int lit_j = __shfl(lit, j), f_j = __shfl(first, j);
-        if (t < ndt) {
-            const int u = (ls_j >> 4) + t - f_j;
+            for (int k = 0; k < 4; ++k)
+                x[k] = __builtin_amdgcn_alignbyte(sw[k + 1], sw[k], (uint32_t)sp);
+            if (e - v == 4) {
+                reinterpret_cast<uint4 *>(dst)[u] = make_uint4(x[0], x[1], x[2], x[3]);
+            } else {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int w = 4 * u + k;
-                const int b0 = ls_j - 4 * w, b1 = b0 + ll_j; // the run's bytes in dword w: [b0, b1)
-                if (b1 > 0 && b0 < 4) {
-                    const uint32_t val = lds_le32_head(b32, lit_j - b0);
-                    if (b0 <= 0 && b1 >= 4) {
-                        dst32[w] = val;
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (i >= b0 && i < b1) dst[4 * w + i] = (uint8_t)(val >> (8 * i));
-                    }
-                }
+                for (int k = 0; k < 3; ++k)
+                    if (v + k < e) dst32[v + k] = x[k];
             }
         }
     }
@@ -401,56 +434,40 @@ __device__ __forceinline__ int emit_sequences(uint8_t *__restrict__ dst, int op,
 
 // ---- the fixed-rule LZ4 encoder of one LDS-resident block -----------------
 // Length of the common prefix of b[q + L ...] and b[c + L ...] (c < q),
-// capped at maxL: 256 bytes per step first, then 1 KiB per step.  Bytes at or
-// beyond maxL count as mismatches.
-template <int MAXB>
-__device__ __forceinline__ int extend_match(const uint32_t *b32, int c, int q, int L, int maxL)
+// capped at maxL: 256 bytes in the first step, then 1 KiB per step.  No step
+// looks at the cap: bytes at or past it (as far as 1 KiB past the block, in
+// the table) are compared with the rest, and the cap is taken at the end.
+__device__ __forceinline__ int extend_match(const uint32_t *b32, int c, int q, int L, int maxL,
+                                            int lane)
 {
-    const int lane = lane_id();
-    if (L >= maxL) return maxL;
-    if (L + 4 * kWave <= maxL) {
-        // the whole first step lies inside the block and the limit
+    {
         const int o = L + 4 * lane;
         const uint32_t diff = lds_le32(b32, c + o) ^ lds_le32(b32, q + o);
-        const uint64_t mm = __ballot(diff != 0);
+        const uint64_t mm = ballot(diff != 0);
         if (mm) {
             const int fl = __builtin_ctzll(mm);
             const uint32_t dd = (uint32_t)__builtin_amdgcn_readlane((int)diff, fl);
-            return L + 4 * fl + (__builtin_ctz(dd) >> 3);
-        }
-        L += 4 * kWave;
-    } else {
-        const int o = L + 4 * lane;
-        const int pa = c + o < MAXB ? c + o : MAXB;
-        const int pb = q + o < MAXB ? q + o : MAXB;
-        uint32_t diff = lds_le32(b32, pa) ^ lds_le32(b32, pb);
-        const int vb = maxL - o;
-        if (vb < 4) diff |= vb <= 0 ? 0xFFFFFFFFu : (0xFFFFFFFFu << (8 * vb));
-        const uint64_t mm = __ballot(diff != 0);
-        if (mm) {
-            const int fl = __builtin_ctzll(mm);
-            const uint32_t dd = (uint32_t)__builtin_amdgcn_readlane((int)diff, fl);
-            return L + 4 * fl + (__builtin_ctz(dd) >> 3);
+            const int len = L + 4 * fl + (__builtin_ctz(dd) >> 3);
+            return len < maxL ? len : maxL;
         }
         L += 4 * kWave;
     }
     while (L < maxL) {
-        const int o = L + 16 * lane;
-        int first = 16; // first differing byte of this lane's 16, 16 = none
+        const int pa = c + L + 16 * lane, pb = q + L + 16 * lane;
+        const uint32_t *wa = b32 + (pa >> 2), *wb = b32 + (pb >> 2);
+        uint32_t diff[4];
 #pragma unroll
-        for (int j = 3; j >= 0; --j) {
-            const int oj = o + 4 * j;
-            const int pa = c + oj < MAXB ? c + oj : MAXB;
-            const int pb = q + oj < MAXB ? q + oj : MAXB;
-            uint32_t diff = lds_le32(b32, pa) ^ lds_le32(b32, pb);
-            const int vb = maxL - oj;
-            if (vb < 4) diff |= vb <= 0 ? 0xFFFFFFFFu : (0xFFFFFFFFu << (8 * vb));
-            if (diff) first = 4 * j + (__builtin_ctz(diff) >> 3);
-        }
-        const uint64_t mm = __ballot(first < 16);
+        for (int j = 0; j < 4; ++j)
+            diff[j] = __builtin_amdgcn_alignbyte(wa[j + 1], wa[j], (uint32_t)pa) ^
+                      __builtin_amdgcn_alignbyte(wb[j + 1], wb[j], (uint32_t)pb);
+        const uint64_t mm = ballot((diff[0] | diff[1] | diff[2] | diff[3]) != 0);
         if (mm) {
             const int fl = __builtin_ctzll(mm);
-            return L + 16 * fl + __builtin_amdgcn_readlane(first, fl);
+            const uint32_t x = diff[0] ? diff[0] : diff[1] ? diff[1] : diff[2] ? diff[2] : diff[3];
+            const int j = diff[0] ? 0 : diff[1] ? 4 : diff[2] ? 8 : 12;
+            const int len = L + 16 * fl +
+                            __builtin_amdgcn_readlane(j + (__builtin_ctz(x) >> 3), fl);
+            return len < maxL ? len : maxL;
         }
         L += 16 * kWave;
     }
@@ -465,14 +482,15 @@ __device__ __forceinline__ int extend_match(const uint32_t *b32, int c, int q, i
 // a chunk the parse enters, (4) parse greedily with the candidates in VGPRs
 // and the match masks in SGPRs.
 // Hash and insert the kGroup positions from g0 (the fixed rule of the LZ4
-// stage): per chunk cc of 64 positions, cand holds the table entry (position
-// + 1, 0 = none) each lane's position found before the chunk's own inserts.
+// stage): per chunk cc of 64 positions, candv[cc] holds the table entry (position
+// + 1, 0 = none) each lane's position found before the chunk's own inserts
+// (0 past last_take, where no match may start).
 // FULL: the whole group lies at or below last_take, so the bound checks drop
 // out, and as g0 is a multiple of 4 every chunk's loads share one base with
 // immediate offsets.
 template <int MAXB, bool FULL>
-__device__ __forceinline__ void hash_group(const uint32_t *b32, uint32_t *table, int g0, int last_q,
-                                           int last_ins, u32x16 &candv)
+__device__ __forceinline__ void hash_group(const uint32_t *b32, uint32_t *table, int g0,
+                                           int last_take, int last_ins, u32x16 &candv)
 {
     constexpr int NC = kGroup / kChunk;
     const int lane = lane_id();
@@ -483,16 +501,16 @@ __device__ __forceinline__ void hash_group(const uint32_t *b32, uint32_t *table,
         const int p = g0 + cc * kChunk + lane;
         const int pc = FULL || p < MAXB ? p : MAXB;
         const uint32_t *d = FULL ? dg + cc * (kChunk / 4) : b32 + (pc >> 2);
-        vv[cc] = __builtin_amdgcn_alignbyte(d[1], d[0], (uint32_t)(pc & 3));
+        vv[cc] = __builtin_amdgcn_alignbyte(d[1], d[0], (uint32_t)pc);
     }
     const auto chunk = [&](int cc) {
-        // (chunks past last_q only insert positions that no lookup sees)
+        // (chunks past last_take only insert positions that no lookup sees)
         const int c0 = g0 + cc * kChunk;
         const int p = c0 + lane;
         const uint32_t v = vv[cc];
         const uint32_t h = (v * kHashMult) >> (32 - kHashBits);
         const uint32_t t = table[h];
-        candv[cc] = FULL || p <= last_q ? t : 0u;
+        candv[cc] = FULL || p <= last_take ? t : 0u;
         // In a run of equal 4-byte values (a constant bit plane) only the
         // run's last position writes: the entry takes the largest position
         // either way, and atomics of many lanes on one address would be
@@ -516,7 +534,7 @@ __device__ __forceinline__ void hash_group(const uint32_t *b32, uint32_t *table,
         uint32_t x = 0;
 #pragma unroll
         for (int cc = 0; cc < NC; ++cc) x |= vv[cc] ^ v0;
-        if (__ballot(x != 0) == 0) {
+        if (ballot(x != 0) == 0) {
 #pragma unroll
             for (int cc = 1; cc < NC; ++cc) candv[cc] = (uint32_t)(g0 + cc * kChunk);
             if (lane == kWave - 1)
@@ -529,28 +547,23 @@ __device__ __forceinline__ void hash_group(const uint32_t *b32, uint32_t *table,
 }
 
 // The mask of the chunk's positions (from c0, a multiple of 64) whose
-// candidate matches for kMinTake = 12 bytes and may be taken (<= last_take).
+// candidate (cand: position + 1, 0 = none) matches for kMinTake = 12 bytes.
 // Branch-free: a lane without a candidate reads position 0 and is masked
 // after.
 __device__ __forceinline__ uint64_t verify_chunk(const uint32_t *b32, int c0, uint32_t cand,
-                                                 int last_take)
+                                                 int lane)
 {
-    const int p = c0 + lane_id();
-    const uint32_t cn = c0 + kChunk - 1 <= last_take || p <= last_take ? cand : 0u;
-    const int c = cn != 0 ? (int)cn - 1 : 0;
-    const uint32_t *o = b32 + (p >> 2);
+    const uint32_t c = cand != 0 ? cand - 1u : 0u;
+    const uint32_t *o = b32 + (c0 >> 2) + (lane >> 2);
     const uint32_t *d = b32 + (c >> 2);
     const uint32_t o0 = o[0], o1 = o[1], o2 = o[2], o3 = o[3];
     const uint32_t e0 = d[0], e1 = d[1], e2 = d[2], e3 = d[3];
-    // zero when the candidate exists and its 12 bytes equal those at p
-    const uint32_t x = (__builtin_amdgcn_alignbyte(e1, e0, (uint32_t)(c & 3)) ^
-                        __builtin_amdgcn_alignbyte(o1, o0, (uint32_t)(p & 3))) |
-                       (__builtin_amdgcn_alignbyte(e2, e1, (uint32_t)(c & 3)) ^
-                        __builtin_amdgcn_alignbyte(o2, o1, (uint32_t)(p & 3))) |
-                       (__builtin_amdgcn_alignbyte(e3, e2, (uint32_t)(c & 3)) ^
-                        __builtin_amdgcn_alignbyte(o3, o2, (uint32_t)(p & 3))) |
-                       ((cn - 1u) >> 31);
-    return __ballot(x == 0);
+    const uint32_t p = (uint32_t)lane;
+    // a candidate, and its 12 bytes equal those at the position
+    return ballot(__builtin_amdgcn_alignbyte(e1, e0, c) == __builtin_amdgcn_alignbyte(o1, o0, p)) &
+           ballot(__builtin_amdgcn_alignbyte(e2, e1, c) == __builtin_amdgcn_alignbyte(o2, o1, p)) &
+           ballot(__builtin_amdgcn_alignbyte(e3, e2, c) == __builtin_amdgcn_alignbyte(o3, o2, p)) &
+           ballot(cand != 0);
 }
 
 // Greedy parse of one LDS-resident block of n bytes (n <= MAXB) into LZ4
@@ -559,7 +572,19 @@ __device__ __forceinline__ uint64_t verify_chunk(const uint32_t *b32, int c0, ui
 // are verified only when the parse reaches it, so chunks inside a long
 // match are never verified.  Sequences are written 64 at a time.
 // (The group's candidates sit in a 16-wide register vector: a uniform index
-// into one compiles to a relative register move.)
+// into one compiles to a relative register move, into an 8-wide one to a
+// chain of selects.  They are defined and used inside one trip of the group
+// loop: carried round a loop they would be copied on every trip.)
+//
+// Bound by issue and by the serial chain about equally: of a wave's 76,000
+// cycles per 8 KiB block of a rounded CHIME-shaped chunk (14.5 waves on a
+// CU) it issues for 41 %, waits for operands for 37 % and for its turn for
+// 22 %; a CU's vector units are 67 % busy, scalar 55 %, LDS 62 %.  So work
+// is taken out of all three: limits are applied to results instead of to
+// every lane's addresses (extend_match, verify_chunk), the emission finds
+// its sequences without a search, and it is inlined once.  Vector
+// instructions per block 4491 -> 3471, scalar 3151 -> 2863; compress call
+// on the 2.16 GB chunk 2.49 -> 2.22 ms, a call of 36 blocks 60 -> 53 us.
 template <int MAXB>
 __device__ __forceinline__ int encode_block(const uint32_t *b32, int n, uint32_t *table,
                                             uint8_t *__restrict__ dst)
@@ -575,55 +600,63 @@ __device__ __forceinline__ int encode_block(const uint32_t *b32, int n, uint32_t
     const int last_take = last_q - (kMinTake - 7); // ... and still reach kMinTake bytes
                                                    // before the last 5 literals
     const int last_ins = n - kMinMatch;        // last position with a defined hash
-    int anchor = 0, pnext = 0, op = 0;
+    int anchor = 0, pos = 0, op = 0; // pos: where the parse stands
     // sequences found and not yet written: lane j holds sequence j
     int ns = 0, s_lit = 0, s_ll = 0, s_off = 0, s_ml = 0;
-    for (int g0 = 0; g0 <= last_q; g0 += kGroup) {
+    for (int g0 = 0;; g0 += kGroup) {
         u32x16 candv;
+        int gend; // the end of the group's parse
         // a group whose every position (and the one after it) may be
         // inserted, looked up and taken needs no bound checks
-        if (g0 + kGroup <= last_take)
-            hash_group<MAXB, true>(b32, table, g0, last_q, last_ins, candv);
-        else
-            hash_group<MAXB, false>(b32, table, g0, last_q, last_ins, candv);
-
-        // chunk by chunk from the one holding the parse position
-        for (int cc = (pnext > g0 ? pnext - g0 : 0) >> 6; cc < NC; ++cc) {
-            const int c0 = g0 + cc * kChunk;
-            if (c0 > last_take) break;
-            const uint64_t mk = verify_chunk(b32, c0, candv[cc], last_take);
-            for (;;) {
-                const int rel = pnext - c0;
-                const uint64_t mm = rel > 0 ? mk & (~0ull << rel) : mk;
-                if (mm == 0) break;
-                const int bit = __builtin_ctzll(mm);
-                const int q = c0 + bit;
-                const int c = __builtin_amdgcn_readlane((int)candv[cc], bit) - 1;
-                const int L = __builtin_amdgcn_readfirstlane(
-                    extend_match<MAXB>(b32, c, q, kMinTake, n - kLastLiterals - q));
+        if (g0 + kGroup <= last_take) {
+            hash_group<MAXB, true>(b32, table, g0, last_take, last_ins, candv);
+            gend = g0 + kGroup;
+        } else {
+            hash_group<MAXB, false>(b32, table, g0, last_take, last_ins, candv);
+            gend = last_take + 1;
+        }
+        bool flush;
+        do { // (twice where the lanes are full before the group's end)
+            while (pos < gend) {
+                // the chunk holding the parse position
+                const int c0 = pos & -kChunk;
+                const uint32_t cand = candv[(pos - g0) >> 6];
+                uint64_t mk = verify_chunk(b32, c0, cand, lane);
+                // its matches from pos on (the shift takes the low 6 bits of pos)
+                while ((mk &= ~0ull << (pos & (kChunk - 1))) != 0) {
+                    const int bit = __builtin_ctzll(mk);
+                    const int q = c0 + bit;
+                    const int c = __builtin_amdgcn_readlane((int)cand, bit) - 1;
+                    const int L =
+                        uni(extend_match(b32, c, q, kMinTake, n - kLastLiterals - q, lane));
+                    const bool me = lane == ns;
+                    s_lit = me ? anchor : s_lit;
+                    s_ll = me ? q - anchor : s_ll;
+                    s_off = me ? q - c : s_off;
+                    s_ml = me ? L : s_ml;
+                    ++ns;
+                    anchor = pos = q + L;
+                    if (pos >= c0 + kChunk || ns == kWave) break;
+                }
+                if (ns == kWave) break;
+                if (pos < c0 + kChunk) pos = c0 + kChunk;
+            }
+            const bool last = g0 + kGroup > last_q && pos >= gend && ns < kWave;
+            if (last) { // the last literals
                 const bool me = lane == ns;
                 s_lit = me ? anchor : s_lit;
-                s_ll = me ? q - anchor : s_ll;
-                s_off = me ? q - c : s_off;
-                s_ml = me ? L : s_ml;
-                if (++ns == kWave) {
-                    op = emit_sequences(dst, op, b32, ns, s_lit, s_ll, s_off, s_ml);
-                    ns = 0;
-                }
-                pnext = q + L;
-                anchor = pnext;
-                if (pnext >= c0 + kChunk) break;
+                s_ll = me ? n - anchor : s_ll;
+                s_ml = me ? 0 : s_ml;
+                ++ns;
             }
-            // skip the chunks the match covers (the loop steps to the next)
-            if (pnext >= c0 + kChunk) cc = (pnext - g0 - kChunk) >> 6;
-        }
+            flush = last || ns == kWave;
+            if (flush) {
+                op = emit_sequences(dst, op, b32, ns, s_lit, s_ll, s_off, s_ml);
+                ns = 0;
+                if (last) return op;
+            }
+        } while (flush);
     }
-    // the last literals
-    const bool me = lane == ns;
-    s_lit = me ? anchor : s_lit;
-    s_ll = me ? n - anchor : s_ll;
-    s_ml = me ? 0 : s_ml;
-    return emit_sequences(dst, op, b32, ns + 1, s_lit, s_ll, s_off, s_ml);
 }
 
 // ---- sizes -> offsets -------------------------------------------------------
@@ -850,8 +883,6 @@ __device__ __forceinline__ void dmatch(uint32_t *b32, int op, int off, int len)
 // input sits at the tail of the buffer).  Returns false on malformed input:
 // every length, offset and the input/output boundaries are checked once per
 // sequence, and the output may never reach input not yet read.
-__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-
 // The bytes from position pos of the buffer as a wave-uniform little-endian
 // 64-bit value (byte pos in bits 0-7): the two dwords holding pos, so at
 // least the 5 bytes pos .. pos + 4 are valid.
@@ -1049,9 +1080,11 @@ __device__ __forceinline__ void copy_slot(uint8_t *__restrict__ dst, const uint8
 // 10 KiB for the 8 KiB block, exactly 20 of the 512-byte units LDS is
 // allocated in (16 workgroups per CU).  Reads that run past the block land
 // in the table and are masked out.
+// (One array, the table behind the block.)
 template <int MAXB> struct EncLds {
-    uint32_t blk32[MAXB / 4];
-    uint32_t table[1 << kHashBits];
+    uint32_t w[MAXB / 4 + (1 << kHashBits)];
+    __device__ uint32_t *blk32() { return w; }
+    __device__ uint32_t *table() { return w + MAXB / 4; }
 };
 
 // Transpose (and optionally round) the elems x E bytes at src into LDS, then
@@ -1062,9 +1095,9 @@ __device__ __forceinline__ int encode_one(const uint8_t *__restrict__ src, int64
                                           const RoundParams &rp, int64_t first_elem,
                                           uint8_t *__restrict__ slot, EncLds<MAXB> &L)
 {
-    stage_block<EC, RM>(src, elems, E, reinterpret_cast<uint8_t *>(L.blk32), rp, first_elem);
+    stage_block<EC, RM>(src, elems, E, reinterpret_cast<uint8_t *>(L.blk32()), rp, first_elem);
     wave_sync();
-    const int sz = encode_block<MAXB>(L.blk32, (int)(elems * E), L.table, slot);
+    const int sz = encode_block<MAXB>(L.blk32(), (int)(elems * E), L.table(), slot);
     wave_sync();
     return sz;
 }

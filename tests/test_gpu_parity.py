@@ -238,6 +238,22 @@ def test_compress_many_sequences(bsg, E, nb):
     assert np.array_equal(back[: n * E], data)
 
 
+@pytest.mark.parametrize("lit_max", [1, 3, 9, 40, 300])
+def test_compress_literal_runs(bsg, lit_max):
+    """Literal runs of 0 .. lit_max bytes at every alignment (the copies of a
+    run's ends and of its whole dwords, a run inside one dword, more 16-byte
+    units than the wave has lanes) and matches longer than an extension step."""
+    E, nb = 4, 2048
+    P = synth.gen_short_matches(nb * E * 4 + 200, 70 + lit_max, lit_max=lit_max, match_lo=12,
+                                match_hi=12 + 4 * lit_max)
+    P[nb * E + 100: nb * E + 2800] = 0x5A  # one block with a long run, its end inside a step
+    n = P.size // E
+    data = oracle.bitunshuffle(P[: n * E], E, nb)
+    ref = oracle.compress(data, E, nb)
+    got = host(bsg.compress_sync(dev(data), E, nb))
+    assert got.size == ref.size and np.array_equal(got, ref)
+
+
 def _segmented_input():
     # 50,000 blocks of 512 bytes plus a ragged end: three segments of at
     # least 16,384 blocks, so the encoder runs in segments on two streams
