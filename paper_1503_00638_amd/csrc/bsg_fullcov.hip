@@ -5,16 +5,32 @@
 // freedom s_k^2 = 1 / (C^-1)_kk, and the rounding of Section 3.2 with
 // G2 = 12 f s_k^2.  With Q = 2N C this is G2 = c / (Q^-1)_kk, c = (12 f)/(2N).
 //
-// One workgroup per sample holds Q in LDS (D = I^2 <= 121, so at most
-// 120 KiB): the Hermitian V of the sample, the lower triangle of Q from it,
-// a right-looking Cholesky factorisation Q = L L^T in place (a step per
-// column, the trailing update spread over the workgroup), then M = L^-1 one
-// column per thread, a few rows per pass (stored transposed in the free
-// upper triangle) and (Q^-1)_kk = sum_i M_ik^2.  Every element sees its
-// operations in the same order as a plain serial implementation (sums in
-// increasing index order), so the results are reproducible bit for bit.  A
-// sample whose Q is not positive definite gets no estimate and is left
-// unchanged.
+// A grid of G x G threads takes one sample and keeps its matrices in
+// registers: thread (r, c) holds the elements (G a + r, G b + c), a >= b, of
+// the lower triangle of Q, NT x NT tiles with G NT >= D = I^2.  A step of the
+// right-looking Cholesky factorisation Q = L L^T (and then of the inverse
+// M = L^-1, row by row) passes one column (and one row) through LDS and is
+// otherwise NT^2 / 2 independent multiply-subtracts per thread, without an
+// LDS access per element; the step's D divisions go one to a thread.
+// (Q^-1)_kk = sum_i M_ik^2.  Up to 8 inputs a sample is one wavefront (G = 8,
+// no barriers), above that a workgroup of four (G = 16).
+//
+// What bounds it: with the elements in LDS (one workgroup per sample, 256 or
+// 512 threads) every multiply-subtract paid an LDS read and write and every
+// column two barriers: 7.36 ms for 65,536 samples of 8 inputs (1.56 TFLOP/s)
+// and 16.3 ms for 16,384 of 11.  With them in registers 1.54 and 2.92 ms
+// (7.5 and 6.6 TFLOP/s): vector issue (about 240 multiplies and subtracts
+// per thread against a square root, two divisions and four LDS round trips
+// per column), four waves per SIMD (128 VGPRs) hiding the chain.  The chain
+// alone, 16 samples in a call: 51 us (8 inputs, 102 before), 128 us (11,
+// 258 before).  The tile count follows the input count because its loops
+// are unrolled: a smaller array does not carry a larger one's tiles.
+//
+// Every element sees its operations in the same order as a plain serial
+// implementation (sums in increasing index order, products and sums rounded
+// separately), so the results are reproducible bit for bit.  (Zeros may
+// differ in sign on the way, which no nonzero value sees.)  A sample whose Q
+// is not positive definite gets no estimate and is left unchanged.
 #include <cmath>
 
 #include "bsg_internal.hpp"
@@ -24,14 +40,7 @@ namespace bsg {
 
 namespace {
 
-constexpr int kMaxInputs = 11; // D = 121 degrees of freedom, 120 KiB of LDS
-static_assert(kMaxInputs * kMaxInputs <= 128, "the trailing update keeps 8 columns per thread");
-// Up to this many degrees of freedom (8 inputs, four samples per CU) the
-// instance has 256 threads and its inverse forms ROWS = 8 rows of a column
-// per pass (16 would cost occupancy); above it (one sample per CU) 512
-// threads hide more latency in the factorisation, and 2 rows per pass were
-// faster than 4.
-constexpr int kFourRowMaxD = 64;
+constexpr int kMaxInputs = 11; // D = 121 degrees of freedom
 
 struct Cplx {
     double re, im;
@@ -42,15 +51,16 @@ __device__ __forceinline__ Cplx mul_conj(Cplx a, Cplx b) // a * conj(b)
     return Cplx{a.re * b.re + a.im * b.im, a.im * b.re - a.re * b.im};
 }
 
-// inputs (i, j) of product p in upper-triangle row-major order
-__device__ __forceinline__ void pair_of(int I, int p, int &i, int &j)
+// Degree of freedom k of I inputs as i | j << 8 | (Im ? 1 << 16 : 0).  The
+// products (i, i), (i, i + 1), .. of row i have 2 (I - i) - 1 of them, so row
+// i starts at I^2 - (I - i)^2.
+__device__ __forceinline__ int dof_of(int I, int k)
 {
-    i = 0;
-    while (p >= I - i) {
-        p -= I - i;
-        ++i;
-    }
-    j = i + p;
+    int n = (int)__builtin_sqrtf((float)(I * I - k));
+    while (n * n < I * I - k) ++n;
+    while (n > 1 && (n - 1) * (n - 1) >= I * I - k) --n;
+    const int i = I - n, o = k - (I * I - n * n);
+    return i | (i + ((o + 1) >> 1)) << 8 | (o > 0 && !(o & 1) ? 1 << 16 : 0);
 }
 
 struct FullcovArgs {
@@ -63,41 +73,32 @@ struct FullcovArgs {
     double *qdiag;    // [F][T][D] or nullptr
 };
 
-template <int ROWS, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_fullcov(FullcovArgs a)
+// Orders a sample's LDS accesses: a barrier, or a fence where one wavefront
+// owns the sample (its LDS accesses complete in order).
+template <int G> __device__ __forceinline__ void sample_sync()
 {
-    extern __shared__ double smem[];
+    if constexpr (G * G == kWave)
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    else
+        __syncthreads();
+}
+
+template <int G, int NT>
+__global__ __launch_bounds__(G * G) void k_fullcov(FullcovArgs a)
+{
+    constexpr int N = G * NT;
+    static_assert(N <= G * G, "a thread per row");
+    __shared__ double raw[N], col[N], row[N], diag[N];
+    __shared__ Cplx V[N]; // I x I
+    __shared__ int dof[N];
     const int D = a.D, I = a.I, P = a.P;
-    // Q: D x D, row major with rows of LD doubles, LD even: the inverse's
-    // lanes walk rows LD + 1 doubles apart (an odd stride spreads them over
-    // the LDS banks); the factorisation reads column k from its copy colk
-    const int LD = D + (D & 1);
-    double *Q = smem;
-    double *colk = Q + D * LD;            // D: column k of L during step k
-    Cplx *V = reinterpret_cast<Cplx *>(colk + D); // I x I
-    int *dof = reinterpret_cast<int *>(V + I * I);  // D: product * 2 + (Im ? 1 : 0)
-    int *dij = dof + D;                             // D: the product's inputs, i | j << 8
-    __shared__ int bad;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, r = tid / G, c = tid % G;
     const int64_t s = blockIdx.x; // sample (fr, t)
     const int64_t fr = s / a.T, t = s - fr * a.T;
 
-    if (tid == 0) {
-        bad = 0;
-        int k = 0;
-        for (int p = 0; p < P; ++p) {
-            int i, j;
-            pair_of(I, p, i, j);
-            dij[k] = i | j << 8;
-            dof[k++] = 2 * p;
-            if (i != j) {
-                dij[k] = i | j << 8;
-                dof[k++] = 2 * p + 1;
-            }
-        }
-    }
-    for (int e = tid; e < I * I; e += blockDim.x) {
-        const int x = e / I, y = e - x * I;
+    if (tid < N) dof[tid] = tid < D ? dof_of(I, tid) : 0;
+    if (tid < D) {
+        const int x = tid / I, y = tid - x * I;
         Cplx v;
         if (x == y) {
             v.re = a.autos[(fr * I + x) * a.T + t];
@@ -109,147 +110,138 @@ __global__ __launch_bounds__(THREADS) void k_fullcov(FullcovArgs a)
             v.re = w.x;
             v.im = x < y ? (double)w.y : -(double)w.y;
         }
-        V[e] = v;
+        V[tid] = v;
     }
-    __syncthreads();
+    sample_sync<G>();
 
-    // Q = 2N C (Eqs. rad_full1-3), its lower triangle only (the factorisation
-    // reads nothing else, and the inverse writes the upper half before it
-    // reads it); element e of the triangle in row-major order is (x, y),
-    // y <= x, from a float estimate of the row corrected by exact checks.
-    // Each degree of freedom's inputs come from the table built above.
-    for (int e = tid; e < D * (D + 1) / 2; e += blockDim.x) {
-        int x = (int)((__builtin_sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
-        while (x * (x + 1) / 2 > e) --x;
-        while ((x + 1) * (x + 2) / 2 <= e) ++x;
-        const int y = e - x * (x + 1) / 2;
-        const int i = dij[x] & 255, j = dij[x] >> 8, g = dij[y] & 255, h = dij[y] >> 8;
-        const bool ix = dof[x] & 1, iy = dof[y] & 1;
-        const Cplx A = mul_conj(V[i * I + g], V[j * I + h]);
-        const Cplx B = mul_conj(V[i * I + h], V[j * I + g]);
-        double q;
-        if (!ix && !iy) {
-            q = A.re + B.re;
-        } else if (ix && iy) {
-            q = A.re - B.re;
-        } else if (!ix) {
-            q = -A.im + B.im;
-        } else { // (Im ij, Re gh) is the (Re gh, Im ij) element
-            const Cplx A2 = mul_conj(V[g * I + i], V[h * I + j]);
-            const Cplx B2 = mul_conj(V[g * I + j], V[h * I + i]);
-            q = -A2.im + B2.im;
-        }
-        Q[x * LD + y] = q;
-    }
-    __syncthreads();
-
-    // Cholesky, right-looking, in place in the lower triangle
-    for (int k = 0; k < D; ++k) {
-        const double d = Q[k * LD + k];
-        if (!(d > 0.0) || d == __builtin_inf()) { // uniform: every thread reads the same d
-            if (tid == 0) bad = 1;
-            break;
-        }
-        // (only the threads that scale the column, and thread 0, need L_kk:
-        // a wave with none of them skips the square root)
-        double lkk = 0.0;
-        if (k + 1 + tid < D || tid == 0) lkk = sqrt(d);
-        for (int i = k + 1 + tid; i < D; i += blockDim.x) {
-            const double lik = Q[i * LD + k] / lkk;
-            Q[i * LD + k] = lik;
-            colk[i] = lik;
-        }
-        __syncthreads();
-        // every thread has read Q[k][k] before the barrier, and the trailing
-        // update below does not touch it
-        if (tid == 0) Q[k * LD + k] = lkk;
-        // trailing lower triangle, rows and columns k+1 .. D-1, on a
-        // (THREADS / 16) x 16 grid of threads; a thread's columns j0 + 16 b
-        // are the same for all its rows, so their column-k values stay in
-        // registers (D <= 128)
-        const int j0 = k + 1 + (tid & 15);
-        double cj[8];
+    // Q = 2N C (Eqs. rad_full1-3): with A = V_ig conj(V_jh) and B = V_ih
+    // conj(V_jg), Re A + Re B between two real parts, Re A - Re B between two
+    // imaginary parts, Im B - Im A for (Re ij, Im gh), Im B + Im A for
+    // (Im ij, Re gh).
+    double q[NT][NT];
+    {
+        int rd[NT], cd[NT];
 #pragma unroll
-        for (int b = 0; b < 8; ++b) cj[b] = j0 + 16 * b < D ? colk[j0 + 16 * b] : 0.0;
-        for (int i = k + 1 + (tid >> 4); i < D; i += THREADS / 16) {
-            const double lik = colk[i];
+        for (int x = 0; x < NT; ++x) {
+            rd[x] = dof[G * x + r];
+            cd[x] = dof[G * x + c];
+        }
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const int j = j0 + 16 * b;
-                if (j > i) break;
-                Q[i * LD + j] = Q[i * LD + j] - lik * cj[b];
+        for (int x = 0; x < NT; ++x) {
+            const int i = rd[x] & 255, j = rd[x] >> 8 & 255, ix = rd[x] >> 16;
+#pragma unroll
+            for (int y = 0; y <= x; ++y) {
+                const int g = cd[y] & 255, h = cd[y] >> 8 & 255, iy = cd[y] >> 16;
+                const Cplx A = mul_conj(V[i * I + g], V[j * I + h]);
+                const Cplx B = mul_conj(V[i * I + h], V[j * I + g]);
+                const bool same = ix == iy;
+                const double u = same ? A.re : B.im, w = same ? B.re : A.im;
+                q[x][y] = same == (ix == 0) ? u + w : u - w;
             }
         }
-        __syncthreads();
     }
-    __syncthreads();
-    const bool failed = bad != 0;
 
-    // M = L^-1, column j by thread j; M_ij (i > j) kept at Q[j][i]
-    double qk = __builtin_nan("");
-    if (!failed) {
-        for (int j = tid; j < D; j += blockDim.x) {
-            const double mjj = 1.0 / Q[j * LD + j];
-            // (Q^-1)_jj = sum_{i >= j} M_ij^2 in increasing i, added as each
-            // M_ij is formed (its own chain, beside the next row's sum)
-            double q = 0.0;
-            q = q + mjj * mjj;
-            const double *Mj = Q + j * LD; // M_mj at Mj[m]
-            int i = j + 1;
-            // ROWS rows per pass: their sums share the terms m < i, so each
-            // M_mj is read once for all of them, and the sums are independent
-            // chains; every sum still adds its terms one by one in increasing m
-            for (; ROWS > 1 && i + ROWS - 1 < D; i += ROWS) {
-                const double *Lr[ROWS];
-                double acc[ROWS], mv[ROWS];
+    // Cholesky, right-looking: step k = G kb + kc
+    bool bad = false;
 #pragma unroll
-                for (int r = 0; r < ROWS; ++r) {
-                    Lr[r] = Q + (i + r) * LD;
-                    acc[r] = Lr[r][j] * mjj;
-                }
-#pragma unroll 4
-                for (int m = j + 1; m < i; ++m) {
-                    const double mm = Mj[m];
+    for (int kb = 0; kb < NT; ++kb) {
+        for (int kc = 0; kc < G && !bad; ++kc) {
+            const int k = G * kb + kc;
+            if (k >= D) break;
+            if (c == kc) {
 #pragma unroll
-                    for (int r = 0; r < ROWS; ++r) acc[r] = acc[r] + Lr[r][m] * mm;
-                }
-#pragma unroll
-                for (int r = 0; r < ROWS; ++r) {
-#pragma unroll
-                    for (int t = 0; t < r; ++t) acc[r] = acc[r] + Lr[r][i + t] * mv[t];
-                    mv[r] = -acc[r] / Lr[r][i + r];
-                    Q[j * LD + i + r] = mv[r];
-                    q = q + mv[r] * mv[r];
-                }
+                for (int x = kb; x < NT; ++x) raw[G * x + r] = q[x][kb];
             }
-            for (; i < D; ++i) {
-                double acc = Q[i * LD + j] * mjj;
-#pragma unroll 8
-                for (int m = j + 1; m < i; ++m) acc = acc + Q[i * LD + m] * Mj[m];
-                const double mij = -acc / Q[i * LD + i];
-                Q[j * LD + i] = mij;
-                q = q + mij * mij;
+            sample_sync<G>();
+            const double d = raw[k]; // the same for every thread
+            bad = !(d > 0.0) || d == __builtin_inf();
+            const double lkk = sqrt(d);
+            if (tid < N) {
+                const double l = raw[tid] / lkk;
+                col[tid] = tid == k ? lkk : (tid > k && tid < D ? l : 0.0);
             }
-            if (j == tid) qk = q;
-            if (a.qdiag) a.qdiag[s * D + j] = q;
+            if (tid == k) diag[k] = lkk;
+            sample_sync<G>();
+            double ri[NT], cj[NT];
+#pragma unroll
+            for (int x = kb; x < NT; ++x) {
+                ri[x] = col[G * x + r];
+                cj[x] = col[G * x + c];
+            }
+            // column k takes its final values, the columns before it keep theirs
+            if (c <= kc) cj[kb] = 0.0;
+#pragma unroll
+            for (int x = kb; x < NT; ++x) {
+                const double v = q[x][kb] - ri[x] * cj[kb];
+                q[x][kb] = c == kc ? ri[x] : v;
+#pragma unroll
+                for (int y = kb + 1; y <= x; ++y) q[x][y] = q[x][y] - ri[x] * cj[y];
+            }
         }
-    } else if (a.qdiag) {
-        for (int j = tid; j < D; j += blockDim.x) a.qdiag[s * D + j] = __builtin_nan("");
     }
+    sample_sync<G>();
+
+    // M = L^-1: step k = G kb + kc forms row k, M_kj = -(sum_{j <= m < k}
+    // L_km M_mj) / L_kk in thread j, adds its squares to (Q^-1)_jj and its
+    // products with column k of L to the sums of the rows below.
+    double qk = 0.0;
+    if (!bad) {
+        double m[NT][NT];
+#pragma unroll
+        for (int kb = 0; kb < NT; ++kb) {
+#pragma unroll
+            for (int x = kb; x < NT; ++x) m[x][kb] = 0.0;
+            for (int kc = 0; kc < G; ++kc) {
+                const int k = G * kb + kc;
+                if (k >= D) break;
+                if (r == kc) {
+#pragma unroll
+                    for (int y = 0; y <= kb; ++y) raw[G * y + c] = m[kb][y];
+                }
+                if (c == kc) {
+#pragma unroll
+                    for (int x = kb; x < NT; ++x) col[G * x + r] = q[x][kb];
+                }
+                sample_sync<G>();
+                double li[NT];
+#pragma unroll
+                for (int x = kb; x < NT; ++x) li[x] = col[G * x + r];
+                if (tid < N) {
+                    const double num = tid < k ? -raw[tid] : 1.0;
+                    const double v = tid <= k ? num / diag[k] : 0.0;
+                    row[tid] = v;
+                    qk = qk + v * v;
+                }
+                sample_sync<G>();
+#pragma unroll
+                for (int y = 0; y <= kb; ++y) {
+                    const double mj = row[G * y + c];
+#pragma unroll
+                    for (int x = kb; x < NT; ++x) m[x][y] = m[x][y] + li[x] * mj;
+                }
+            }
+        }
+    } else {
+        qk = __builtin_nan("");
+    }
+    if (tid >= D) return;
+    if (a.qdiag) a.qdiag[s * D + tid] = qk;
     if (!a.vis_out) return;
-    // round degree of freedom k = tid (D <= 121 < 256 threads)
-    if (tid < D) {
-        const int p = dof[tid] >> 1;
-        const bool im = dof[tid] & 1;
-        const int64_t e = (fr * P + p) * a.T + t;
-        const float x = im ? a.vis[e].y : a.vis[e].x;
-        const uint32_t r = round_noise_bits(__float_as_uint(x), a.c / qk);
-        float *o = reinterpret_cast<float *>(a.vis_out + e);
-        o[im ? 1 : 0] = __uint_as_float(r);
-        int i, j;
-        pair_of(I, p, i, j);
-        if (i == j) o[1] = a.vis[e].y; // Im of an auto is copied
-    }
+    // round degree of freedom k = tid
+    const int i = dof[tid] & 255, j = dof[tid] >> 8 & 255, im = dof[tid] >> 16;
+    const int p = i * I - i * (i - 1) / 2 + (j - i);
+    const int64_t e = (fr * P + p) * a.T + t;
+    const float x = im ? a.vis[e].y : a.vis[e].x;
+    const uint32_t o = round_noise_bits(__float_as_uint(x), a.c / qk);
+    float *out = reinterpret_cast<float *>(a.vis_out + e);
+    out[im] = __uint_as_float(o);
+    if (i == j) out[1] = a.vis[e].y; // Im of an auto is copied
+}
+
+template <int G, int NT> hipError_t fullcov_launch(const FullcovArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_fullcov<G, NT>), dim3((unsigned)(a.F * a.T)), dim3(G * G), 0, s, a);
+    return hipGetLastError();
 }
 
 } // namespace
@@ -263,14 +255,19 @@ hipError_t launch_fullcov(const float *vis, const float *autos, int64_t F, int64
     if (F * T == 0 || D == 0) return hipSuccess;
     FullcovArgs a{reinterpret_cast<const float2 *>(vis), autos, F, T, (int)I, P, D, c,
                   reinterpret_cast<float2 *>(vis_out), qdiag};
-    const size_t lds = sizeof(double) * ((size_t)D * (D + (D & 1)) + D) +
-                       sizeof(Cplx) * (size_t)(I * I) +
-                       sizeof(int) * (size_t)(2 * D);
-    if (D <= kFourRowMaxD)
-        hipLaunchKernelGGL((k_fullcov<8, 256>), dim3((unsigned)(F * T)), dim3(256), lds, s, a);
-    else
-        hipLaunchKernelGGL((k_fullcov<2, 512>), dim3((unsigned)(F * T)), dim3(512), lds, s, a);
-    return hipGetLastError();
+    switch (I) { // the fewest tiles that hold D
+    case 1:
+    case 2: return fullcov_launch<8, 1>(a, s);
+    case 3:
+    case 4: return fullcov_launch<8, 2>(a, s);
+    case 5: return fullcov_launch<8, 4>(a, s);
+    case 6: return fullcov_launch<8, 5>(a, s);
+    case 7: return fullcov_launch<8, 7>(a, s);
+    case 8: return fullcov_launch<8, 8>(a, s);
+    case 9: return fullcov_launch<16, 6>(a, s);
+    case 10: return fullcov_launch<16, 7>(a, s);
+    default: return fullcov_launch<16, 8>(a, s);
+    }
 }
 
 } // namespace bsg

@@ -53,6 +53,25 @@ def test_fullcov_rounding_parity(bsg, F, I, T, seed, source):
         assert np.array_equal(got.view(np.uint32), ref.view(np.uint32)), f
 
 
+@pytest.mark.parametrize("I", list(range(1, 12)))
+def test_fullcov_every_array_size(bsg, I):
+    """Every number of inputs (each tile count, with and without rows past
+    the degrees of freedom), autos over twelve decades, one sample not
+    positive definite: diagonal and rounding equal the oracle's bits."""
+    vis, autos = synth.gen_vis_point_source(2, I, 5, 40 + I, 0.4)
+    g = (10.0 ** np.random.default_rng(I).uniform(-3, 3, (2, I, 5))).astype(np.float32)
+    pairs = synth.product_pairs(I)
+    vis = (vis * g[:, pairs[:, 0]] * g[:, pairs[:, 1]]).astype(np.complex64)
+    autos = (autos * g * g).astype(np.float32)
+    autos[1, I - 1, 3] = -1.0
+    ref = oracle.fullcov_inverse_diag(vis, autos)
+    got = host(bsg.fullcov_inverse_diag(dev(vis), dev(autos)))
+    assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
+    ref = oracle.round_to_noise_fullcov(vis, autos, N, 0.01)
+    got = host(bsg.round_to_noise_fullcov(dev(vis), dev(autos), N, 0.01))
+    assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
+
+
 def test_fullcov_singular_and_in_place(bsg):
     vis, autos = synth.gen_vis(3, 6, 9, 7)
     autos[1, 2, 4] = 0.0
