@@ -288,7 +288,7 @@ __global__ __launch_bounds__(64) void k_batch_pack(const uint8_t *__restrict__ t
         if (d_nbytes[ch.orig] < 0) continue;
         const int64_t local = g - ch.block_start;
         copy_slot(ch.out + kHeaderBytes + 8 * (ch.n_blocks + 1) + (prefix[g] - prefix[ch.block_start]),
-                  slots + ch.slot_start + local * ch.slot_bytes, sizes[g]);
+                  slots + ch.slot_start + local * ch.slot_bytes, sizes[g], lane_id());
     }
 }
 

@@ -5,8 +5,8 @@
 //
 // Compression = k_encode (transpose into LDS [+ fused rounding], LDS hash
 // table, greedy parse, write to a bound-sized slot) -> k_tile_sum ->
-// k_tile_offsets (one workgroup) -> k_write_offsets -> k_pack (copy slots to
-// their final place, header, raw tail).  A large input is encoded in
+// k_offsets (both left out for small inputs) -> k_pack (copy slots to their
+// final place, raw tail).  A large input is encoded in
 // segments on two streams while a third stream scans and packs each
 // finished segment, so the copy out of the slots runs under the encoding
 // of the next segments (the encoder is bound by instruction issue, the
@@ -40,117 +40,165 @@ __global__ __launch_bounds__(64) void k_encode(EncArgs a, RoundParams rp)
     if (threadIdx.x == 0) a.sizes[b] = sz;
 }
 
-// tile_sum[k] = sum of sizes over blocks [k * kTile, (k + 1) * kTile)
-__global__ __launch_bounds__(256) void k_tile_sum(const int32_t *__restrict__ sizes,
-                                                  int64_t n_blocks, int64_t tile0,
-                                                  int64_t *__restrict__ tile_sum)
+struct PackArgs {
+    const uint8_t *slots;
+    int64_t slot_bytes;
+    const int32_t *sizes;
+    int64_t *tile_sum;
+    int64_t n_blocks, b0; // the launch's first block (a multiple of kTile)
+    int last;             // it goes to the end: header, verdict, raw tail
+    int64_t fixed_bytes, cap;
+    int64_t *d_nbytes;
+    uint8_t *out;
+    uint32_t magic;
+    int64_t n, E, nb;
+    const uint8_t *tail_src;
+    int64_t tail_bytes, tail_first_elem;
+    int round_tail;
+};
+
+__device__ __forceinline__ uint64_t *offsets_of(const PackArgs &a)
 {
-    __shared__ int64_t sh[256];
-    const int64_t tile = tile0 + blockIdx.x;
-    const int64_t base = tile * kTile;
-    int64_t s = 0;
-    for (int k = threadIdx.x; k < kTile; k += 256)
-        if (base + k < n_blocks) s += sizes[base + k];
-    const int64_t inc = block_sum_i64(s, sh);
-    if (threadIdx.x == 255) tile_sum[tile] = inc;
+    return reinterpret_cast<uint64_t *>(a.out + kHeaderBytes);
 }
 
-// One workgroup: exclusive scan of the tile sums of tiles [t0, t1) (in
-// place) after the payload bytes of the tiles before t0 (*carry, 0 when t0 =
-// 0); leaves the payload bytes up to t1 in *carry.  With last set: stream
-// total, capacity verdict, stream header.
-__global__ __launch_bounds__(256) void k_tile_offsets(int64_t *__restrict__ tile_sum,
-                                                      int64_t t0, int64_t t1,
-                                                      int64_t *__restrict__ carry_io, int last,
-                                                      int64_t fixed_bytes, int64_t cap,
-                                                      int64_t *__restrict__ d_nbytes,
-                                                      uint8_t *__restrict__ out, bsg_header hdr)
+// Stream total, capacity verdict, header and the end of the offset table
+// (one thread).
+__device__ __forceinline__ void finish_stream(const PackArgs &a, int64_t payload)
 {
-    __shared__ int64_t sh[256];
-    int64_t carry = t0 > 0 ? *carry_io : 0;
-    for (int64_t base = t0; base < t1; base += 256) {
-        const int64_t k = base + threadIdx.x;
-        const int64_t v = k < t1 ? tile_sum[k] : 0;
-        const int64_t inc = block_sum_i64(v, sh);
-        if (k < t1) tile_sum[k] = carry + inc - v;
-        carry += sh[255];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && !last) *carry_io = carry;
-    if (threadIdx.x == 0 && last) {
-        const int64_t total = fixed_bytes + carry;
-        *d_nbytes = total <= cap ? total : (int64_t)BSG_ECAPACITY;
-        *reinterpret_cast<bsg_header *>(out) = hdr;
-        // payload length at the end of the offset table
-        reinterpret_cast<uint64_t *>(out + kHeaderBytes)[hdr.n_blocks] = (uint64_t)carry;
-    }
+    const int64_t total = a.fixed_bytes + payload;
+    *a.d_nbytes = total <= a.cap ? total : (int64_t)BSG_ECAPACITY;
+    bsg_header *h = reinterpret_cast<bsg_header *>(a.out);
+    h->magic = a.magic;
+    h->elem_size = (uint32_t)a.E;
+    h->n = (uint64_t)a.n;
+    h->block_elems = (uint32_t)a.nb;
+    h->n_blocks = (uint32_t)a.n_blocks;
+    offsets_of(a)[a.n_blocks] = (uint64_t)payload;
 }
 
-// off[b] for every block of a tile (written straight into the stream).
-__global__ __launch_bounds__(256) void k_write_offsets(const int32_t *__restrict__ sizes,
-                                                       int64_t n_blocks, int64_t tile0,
-                                                       const int64_t *__restrict__ tile_off,
-                                                       uint8_t *__restrict__ out)
+// The two scan kernels take one wavefront per 1024-block tile and no LDS:
+// the encoders beside them hold all of it (16 x 10 KiB per CU), and a
+// workgroup that needs some waits until a CU's encoder ends and no other
+// takes its place (a one-workgroup scan waited 1.3 ms; the packs then ran
+// after the encoding instead of beside it).
+//
+// Sizes of tile t: lane l holds blocks 4 l .. 4 l + 3 of each of its 4 strips
+// (0 past the last block; the array is padded to 256 bytes).
+constexpr int kStrip = 4 * kWave;
+__device__ __forceinline__ void load_tile(const PackArgs &a, int64_t tile, int lane,
+                                          int (&v)[kTile / kStrip][4])
 {
-    __shared__ int64_t sh[256];
-    constexpr int PER = kTile / 256;
-    const int64_t tile = tile0 + blockIdx.x;
-    const int64_t base = tile * kTile + threadIdx.x * PER;
-    int64_t v[PER];
-    int64_t s = 0;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        v[k] = base + k < n_blocks ? sizes[base + k] : 0;
-        s += v[k];
-    }
-    const int64_t inc = block_sum_i64(s, sh);
-    int64_t o = tile_off[tile] + inc - s;
-    uint64_t *off = reinterpret_cast<uint64_t *>(out + kHeaderBytes);
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        if (base + k < n_blocks) off[base + k] = (uint64_t)o;
-        o += v[k];
+    for (int s = 0; s < kTile / kStrip; ++s) {
+        const int64_t k = tile * kTile + s * kStrip + 4 * lane;
+        const int4 x = *reinterpret_cast<const int4 *>(a.sizes + (k < a.n_blocks ? k : 0));
+        v[s][0] = k < a.n_blocks ? x.x : 0;
+        v[s][1] = k + 1 < a.n_blocks ? x.y : 0;
+        v[s][2] = k + 2 < a.n_blocks ? x.z : 0;
+        v[s][3] = k + 3 < a.n_blocks ? x.w : 0;
     }
 }
 
-// Copy the LZ4 bytes of blocks block0, block0 + 1, ... from their slots to
-// the payload; block n_blocks (in the last launch) stands for the raw tail.
-// Nothing is written past the output's capacity: a block whose bytes would
-// end past payload_cap is skipped (the stream then does not fit and the
-// call reports so), and the tail is written only when the stream fits
-// (d_nbytes >= 0, known by the time the last launch runs).
-__global__ __launch_bounds__(64) void k_pack(const uint8_t *__restrict__ slots, int64_t slot_bytes,
-                                             const int32_t *__restrict__ sizes, int64_t n_blocks,
-                                             int64_t block0, int64_t payload_cap,
-                                             uint8_t *__restrict__ out,
-                                             const int64_t *__restrict__ d_nbytes,
-                                             const uint8_t *__restrict__ tail_src,
-                                             int64_t tail_bytes, RoundParams rp, int round_tail,
-                                             int64_t tail_first_elem)
+__global__ __launch_bounds__(64) void k_tile_sum(PackArgs a)
 {
-    const int64_t b = block0 + blockIdx.x;
-    const uint64_t *off = reinterpret_cast<const uint64_t *>(out + kHeaderBytes);
-    uint8_t *payload = out + kHeaderBytes + 8 * (n_blocks + 1);
+    const int64_t tile = a.b0 / kTile + blockIdx.x;
+    int v[kTile / kStrip][4], sum = 0, total;
+    load_tile(a, tile, threadIdx.x, v);
+#pragma unroll
+    for (int s = 0; s < kTile / kStrip; ++s) sum += v[s][0] + v[s][1] + v[s][2] + v[s][3];
+    wave_excl_scan(sum, total); // a tile's bytes stay below 2^27
+    if (threadIdx.x == 0) a.tile_sum[tile] = total;
+}
+
+// Offsets of a tile's blocks, after the sums of all tiles before it.
+__global__ __launch_bounds__(64) void k_offsets(PackArgs a)
+{
+    const int64_t tile = a.b0 / kTile + blockIdx.x;
     const int lane = threadIdx.x;
-    if (b == n_blocks) {
-        if (*d_nbytes < 0) return;
-        uint8_t *dst = payload + off[n_blocks];
-        if (round_tail) { // the raw tail of the fused path is rounded too (float32 elements)
-            for (int64_t k = lane; k < tail_bytes / 4; k += kWave) {
-                uint32_t x = 0;
-                for (int q = 0; q < 4; ++q) x |= (uint32_t)tail_src[4 * k + q] << (8 * q);
-                x = round_element(x, tail_first_elem + k, rp);
-                for (int q = 0; q < 4; ++q) dst[4 * k + q] = (uint8_t)(x >> (8 * q));
-            }
-            return;
+    int v[kTile / kStrip][4];
+    load_tile(a, tile, lane, v);
+    int64_t before = 0;
+#pragma unroll 4
+    for (int64_t k = lane; k < tile; k += kWave) before += a.tile_sum[k];
+    // the lanes' 64-bit sums added up in two parts of 24 bits and the rest
+    int lo, hi;
+    wave_excl_scan((int)(before & 0xFFFFFF), lo);
+    wave_excl_scan((int)(before >> 24), hi);
+    int64_t base = ((int64_t)hi << 24) + lo;
+    uint64_t *off = offsets_of(a);
+#pragma unroll
+    for (int s = 0; s < kTile / kStrip; ++s) {
+        const int64_t k = tile * kTile + s * kStrip + 4 * lane;
+        int total;
+        int64_t o = base + wave_excl_scan(v[s][0] + v[s][1] + v[s][2] + v[s][3], total);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (k + q < a.n_blocks) off[k + q] = (uint64_t)o;
+            o += v[s][q];
         }
-        for (int64_t i = lane; i < tail_bytes; i += kWave) dst[i] = tail_src[i];
+        base += total;
+    }
+    if (a.last && blockIdx.x + 1 == gridDim.x && lane == 0) finish_stream(a, base);
+}
+
+// (Each launch moves next to nothing: its 5 us are the launch and two memory
+// round trips, so fewer launches are all that helps.  Before, four scan and
+// pack launches followed the encode: 53.5 -> 47.0 us for a call of 36 blocks,
+// 112 -> 104 us at 2094 blocks, 150 -> 146 us at 15,600.)
+//
+// Copy the LZ4 bytes of blocks b0, b0 + 1, ... from their slots to the
+// payload, one wavefront per block; in the last launch the wavefront past
+// the last block copies the raw tail.  Nothing is written past the output's
+// capacity: a block whose bytes would end past it is skipped (the stream
+// then does not fit and the call reports so), and the tail is written only
+// when the stream fits.
+// SELF: the whole stream in one launch, no scan before it: each
+// wavefront adds up the sizes of the blocks before its own, and the last one
+// writes the header and the verdict too.
+template <bool SELF>
+__global__ __launch_bounds__(64) void k_pack(PackArgs a, RoundParams rp)
+{
+    const int64_t b = a.b0 + blockIdx.x;
+    const int lane = threadIdx.x;
+    uint64_t *off = offsets_of(a);
+    uint8_t *payload = a.out + kHeaderBytes + 8 * (a.n_blocks + 1);
+    const int sz = b < a.n_blocks ? a.sizes[b] : 0;
+    int64_t ob;
+    if constexpr (SELF) {
+        const uint4 *before = reinterpret_cast<const uint4 *>(a.sizes);
+        const int n1 = (int)b, n4 = n1 / 4;
+        uint32_t sum = 4 * n4 + lane < n1 ? a.sizes[4 * n4 + lane] : 0;
+#pragma unroll 8
+        for (int k = lane; k < n4; k += kWave) {
+            const uint4 v = before[k];
+            sum += v.x + v.y + v.z + v.w;
+        }
+        int total;
+        wave_excl_scan((int)sum, total);
+        ob = total;
+        if (lane == 0 && b < a.n_blocks) off[b] = (uint64_t)ob;
+        if (lane == 0 && b == a.n_blocks) finish_stream(a, ob);
+    } else {
+        ob = (int64_t)off[b];
+    }
+    if (b < a.n_blocks) {
+        if (a.fixed_bytes + ob + sz <= a.cap)
+            copy_slot(payload + ob, a.slots + b * a.slot_bytes, sz, lane);
         return;
     }
-    const uint64_t ob = off[b];
-    const int sz = sizes[b];
-    if ((int64_t)(ob + sz) > payload_cap) return;
-    copy_slot(payload + ob, slots + b * slot_bytes, sz);
+    if (a.fixed_bytes + ob > a.cap) return;
+    uint8_t *dst = payload + ob;
+    if (a.round_tail) { // the raw tail of the fused path is rounded too (float32 elements)
+        for (int64_t k = lane; k < a.tail_bytes / 4; k += kWave) {
+            uint32_t x = 0;
+            for (int q = 0; q < 4; ++q) x |= (uint32_t)a.tail_src[4 * k + q] << (8 * q);
+            x = round_element(x, a.tail_first_elem + k, rp);
+            for (int q = 0; q < 4; ++q) dst[4 * k + q] = (uint8_t)(x >> (8 * q));
+        }
+        return;
+    }
+    for (int64_t i = lane; i < a.tail_bytes; i += kWave) dst[i] = a.tail_src[i];
 }
 
 struct DecArgs {
@@ -285,9 +333,15 @@ int64_t compress_workspace(const Layout &L)
     int64_t ws = L.n_blocks * slot;
     ws = (ws + 255) / 256 * 256 + ((L.n_blocks * 4 + 255) / 256) * 256;
     ws += ((n_tiles * 8 + 255) / 256) * 256;
-    ws += 256; // the payload bytes carried from one segment to the next
+    ws += 256; // (spare)
     return ws;
 }
+
+// Up to this many blocks the pack's wavefronts add up the sizes before their
+// own block (at most 16 KiB each, from L2, all loads in flight); above it the
+// two scan launches cost less than the reading, which grows with the square
+// of the count.
+constexpr int64_t kSelfMaxBlocks = 4096;
 
 constexpr int kMaxSeg = kSideEvents;     // segments of a large input
 constexpr int64_t kSegMinBlocks = 8192; // ... of at least this many blocks
@@ -356,15 +410,27 @@ hipError_t launch_compress(const uint8_t *in, uint8_t *out, const Layout &L, int
     int32_t *sizes = reinterpret_cast<int32_t *>(w + pos);
     pos += ((L.n_blocks * 4 + 255) / 256) * 256;
     int64_t *tile_sum = reinterpret_cast<int64_t *>(w + pos);
-    pos += ((n_tiles * 8 + 255) / 256) * 256;
-    int64_t *carry = reinterpret_cast<int64_t *>(w + pos);
 
     RoundParams none{};
     const int ec = filter == BSG_FILTER_BYTE ? kByteShuffle : element_class(L.E);
-    bsg_header hdr{filter == BSG_FILTER_BYTE ? BSG_MAGIC_BYTE : BSG_MAGIC, (uint32_t)L.E,
-                   (uint64_t)L.n, (uint32_t)L.nb, (uint32_t)L.n_blocks};
-    const int64_t fixed = kHeaderBytes + 8 * (L.n_blocks + 1) + L.tail * L.E;
-    const uint8_t *tail_src = in + (L.n - L.tail) * L.E;
+    PackArgs pa{};
+    pa.slots = slots;
+    pa.slot_bytes = slot;
+    pa.sizes = sizes;
+    pa.n_blocks = L.n_blocks;
+    pa.tile_sum = tile_sum;
+    pa.fixed_bytes = kHeaderBytes + 8 * (L.n_blocks + 1) + L.tail * L.E;
+    pa.cap = cap;
+    pa.d_nbytes = d_nbytes;
+    pa.out = out;
+    pa.magic = filter == BSG_FILTER_BYTE ? BSG_MAGIC_BYTE : BSG_MAGIC;
+    pa.n = L.n;
+    pa.E = L.E;
+    pa.nb = L.nb;
+    pa.tail_src = in + (L.n - L.tail) * L.E;
+    pa.tail_bytes = L.tail * L.E;
+    pa.tail_first_elem = L.n - L.tail;
+    pa.round_tail = rp ? 1 : 0;
 
     // segments of whole tiles
     int nseg = (int)std::min<int64_t>(kMaxSeg, L.n_blocks / kSegMinBlocks);
@@ -391,26 +457,22 @@ hipError_t launch_compress(const uint8_t *in, uint8_t *out, const Layout &L, int
         if (g && ((e = hipEventRecord(g->done[i], es)) != hipSuccess ||
                   (e = hipStreamWaitEvent(ps, g->done[i], 0)) != hipSuccess))
             return e;
-        if (t1 > t0) {
-            hipLaunchKernelGGL(k_tile_sum, dim3((unsigned)(t1 - t0)), dim3(256), 0, ps, sizes,
-                               L.n_blocks, t0, tile_sum);
+        pa.b0 = b0;
+        pa.last = last ? 1 : 0;
+        const unsigned npack = (unsigned)(b1 - b0 + (last ? 1 : 0));
+        if (L.n_blocks <= kSelfMaxBlocks) {
+            hipLaunchKernelGGL((k_pack<true>), dim3(npack), dim3(kWave), 0, ps, pa,
+                               rp ? *rp : none);
+        } else {
+            const unsigned nt = (unsigned)(t1 - t0);
+            hipLaunchKernelGGL(k_tile_sum, dim3(nt), dim3(kWave), 0, ps, pa);
             if ((e = hipGetLastError()) != hipSuccess) return e;
+            hipLaunchKernelGGL(k_offsets, dim3(nt), dim3(kWave), 0, ps, pa);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            hipLaunchKernelGGL((k_pack<false>), dim3(npack), dim3(kWave), 0, ps, pa,
+                               rp ? *rp : none);
         }
-        hipLaunchKernelGGL(k_tile_offsets, dim3(1), dim3(256), 0, ps, tile_sum, t0, t1, carry,
-                           last ? 1 : 0, fixed, cap, d_nbytes, out, hdr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (t1 > t0) {
-            hipLaunchKernelGGL(k_write_offsets, dim3((unsigned)(t1 - t0)), dim3(256), 0, ps,
-                               sizes, L.n_blocks, t0, tile_sum, out);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        const int64_t npack = b1 - b0 + (last ? 1 : 0);
-        if (npack > 0) {
-            hipLaunchKernelGGL(k_pack, dim3((unsigned)npack), dim3(kWave), 0, ps, slots, slot,
-                               sizes, L.n_blocks, b0, cap - fixed, out, d_nbytes, tail_src,
-                               L.tail * L.E, rp ? *rp : none, rp ? 1 : 0, L.n - L.tail);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
     }
     // (odd segments went to the encode stream)
     if (g) return side_streams_end(g, s, (nseg & 1) ? nseg - 2 : nseg - 1);

@@ -1033,10 +1033,9 @@ template <int MAXB> constexpr int dec_buf_bytes() { return (MAXB + MAXB / 255 + 
 // dwords plus the dword after them, and one 16-byte store.  All loads are
 // issued before the first store.
 __device__ __forceinline__ void copy_slot(uint8_t *__restrict__ dst, const uint8_t *__restrict__ src,
-                                          int sz)
+                                          int sz, int lane)
 {
     constexpr int kSteps = 4; // 4 KiB per pass of the wave
-    const int lane = lane_id();
     const int mis = (int)((4 - ((uintptr_t)dst & 3)) & 3);
     const int head = mis < sz ? mis : sz;
     if (lane < head) dst[lane] = src[lane];

@@ -589,6 +589,29 @@ def test_decode_rejects_overlong_literals(bsg):
         assert np.array_equal(got[:n], expect) and np.array_equal(got[2 * n:3 * n], expect)
 
 
+@pytest.mark.parametrize("blocks", [0, 1, 3, 4, 5, 1023, 4095, 4096, 4097, 5120, 5121, 9000])
+def test_offsets_at_scan_edges(bsg, blocks):
+    """Block counts around the wavefront, the scan tile and the count above
+    which the offsets come from the scan kernels, with a raw tail; at a
+    capacity one byte short the verdict says so and nothing is written past
+    the capacity."""
+    E, nb = 4, 16
+    n = blocks * nb + 5
+    data = synth.gen_gauss_int32(n, 5, blocks + 1).view(np.uint8)
+    ref = oracle.compress(data, E, nb)
+    got = host(bsg.compress_sync(dev(data), E, nb))
+    assert got.size == ref.size and np.array_equal(got, ref)
+    cap = ref.size - 1
+    buf = torch.full((ref.size + 64,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    if blocks == 0:  # less than the header and the tail: refused at once
+        with pytest.raises(bsg.BsgError):
+            bsg.compress(dev(data), E, nb, out=buf[:cap])
+    else:
+        _, nbytes = bsg.compress(dev(data), E, nb, out=buf[:cap])
+        assert int(nbytes.item()) == bsg.BSG_ECAPACITY
+    assert (host(buf)[cap:] == 0xA5).all()
+
+
 def test_capacity_verdict(bsg):
     x = np.random.default_rng(0).integers(0, 256, 2048 * 4 * 4, dtype=np.uint8)
     ref = oracle.compress(x, 4, 2048)
