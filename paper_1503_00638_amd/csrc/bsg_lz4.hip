@@ -13,6 +13,8 @@
 // copy by HBM).
 // Decompression = k_decode (stage the LZ4 block in LDS, decode into LDS,
 // inverse transpose on the way out to HBM).
+#include <type_traits>
+
 #include "bsg_lz4_dev.hpp"
 
 namespace bsg {
@@ -324,6 +326,15 @@ hipError_t decode_dispatch(const DecArgs &a, int ec, hipStream_t s)
     }
 }
 
+// f(the smallest instance's block size that holds blocks of this many bytes).
+template <typename F> auto for_block_size(int64_t bytes, F f)
+{
+    if (bytes <= kTinyBlock) return f(std::integral_constant<int, kTinyBlock>{});
+    if (bytes <= kSmallBlock) return f(std::integral_constant<int, kSmallBlock>{});
+    if (bytes <= kMidBlock) return f(std::integral_constant<int, kMidBlock>{});
+    return f(std::integral_constant<int, kLargeBlock>{});
+}
+
 } // namespace
 
 int64_t compress_workspace(const Layout &L)
@@ -435,8 +446,8 @@ hipError_t launch_compress(const uint8_t *in, uint8_t *out, const Layout &L, int
     // segments of whole tiles
     int nseg = (int)std::min<int64_t>(kMaxSeg, L.n_blocks / kSegMinBlocks);
     if (nseg > 1 && may_segment) {
-        const int regs = L.block_bytes() <= kSmallBlock ? encoder_vgprs_for<kSmallBlock>(rp, ec)
-                                                        : encoder_vgprs_for<kLargeBlock>(rp, ec);
+        const int regs = for_block_size(
+            L.block_bytes(), [&](auto maxb) { return encoder_vgprs_for<maxb.value>(rp, ec); });
         if (regs > kSegMaxVgprs) nseg = 1;
     }
     if (nseg < 1 || !may_segment) nseg = 1;
@@ -451,8 +462,9 @@ hipError_t launch_compress(const uint8_t *in, uint8_t *out, const Layout &L, int
         const bool last = i == nseg - 1;
         hipStream_t es = (g && (i & 1)) ? g->enc : s;
         EncArgs ea{in, L.nb, L.E, L.n_full, L.last, slots, slot, sizes, b0};
-        e = L.block_bytes() <= kSmallBlock ? encode_dispatch<kSmallBlock>(ea, b1 - b0, rp, ec, es)
-                                           : encode_dispatch<kLargeBlock>(ea, b1 - b0, rp, ec, es);
+        e = for_block_size(L.block_bytes(), [&](auto maxb) {
+            return encode_dispatch<maxb.value>(ea, b1 - b0, rp, ec, es);
+        });
         if (e != hipSuccess) return e;
         if (g && ((e = hipEventRecord(g->done[i], es)) != hipSuccess ||
                   (e = hipStreamWaitEvent(ps, g->done[i], 0)) != hipSuccess))
@@ -486,8 +498,8 @@ hipError_t launch_decompress(const uint8_t *in, int64_t in_nbytes, uint8_t *out,
               L.last, L.n_blocks, L.tail, d_status, ((uintptr_t)out % 16) == 0,
               filter == BSG_FILTER_BYTE ? BSG_MAGIC_BYTE : BSG_MAGIC};
     const int ec = filter == BSG_FILTER_BYTE ? kByteShuffle : element_class(L.E);
-    return L.block_bytes() <= kSmallBlock ? decode_dispatch<kSmallBlock>(a, ec, s)
-                                          : decode_dispatch<kLargeBlock>(a, ec, s);
+    return for_block_size(L.block_bytes(),
+                          [&](auto maxb) { return decode_dispatch<maxb.value>(a, ec, s); });
 }
 
 } // namespace bsg

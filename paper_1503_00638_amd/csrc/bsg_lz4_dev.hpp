@@ -12,7 +12,15 @@ namespace bsg {
 namespace {
 
 
-constexpr int kSmallBlock = 8192;     // LDS-resident block for the hot path
+// Block sizes the kernels have instances for: the batched ones for the default
+// block and the largest, the single-stream ones for two more.  The LDS of a
+// workgroup, and so the blocks in flight on a CU, follows the instance (the
+// encoder's 26, 16, 8 and 2; the decoder's 36, 18, 9 and 2): 4 KiB blocks
+// encoded at 89 us in the 8 KiB instance and 83 in their own (65 MB of 8-byte
+// elements), 16 KiB ones ran 2.7 times as long in the 64 KiB instance.
+constexpr int kTinyBlock = 4096;
+constexpr int kSmallBlock = 8192;
+constexpr int kMidBlock = 16384;
 constexpr int kLargeBlock = 65536;
 constexpr int kTile = 1024;           // blocks per scan tile
 
@@ -1101,14 +1109,17 @@ __device__ __forceinline__ int encode_one(const uint8_t *__restrict__ src, int64
     return sz;
 }
 
-// Waves per SIMD the decoder kernels ask the register allocator for: 4
-// (at most 128 VGPRs) for 8 KiB blocks of element classes up to 8 bytes,
-// where LDS lets 18 blocks reside per CU and one more register would cost
-// a quarter of them; 1 (no limit) where the transpose of 12- and 16-byte
-// elements needs more registers or LDS already allows only a few blocks.
+// Waves per SIMD the decoder kernels ask the register allocator for, of
+// element classes up to 8 bytes: 4 (at most 128 VGPRs) for 8 KiB blocks,
+// where LDS lets 18 blocks reside per CU and one more register would cost a
+// quarter of them; 5 for 4 KiB blocks, where LDS lets 36 reside (8-byte
+// elements, 65 MB: 54.2 us at 127 VGPRs, 50.3 at 85, 51.5 at 80 with spills);
+// 1 (no limit) where the transpose of 12- and 16-byte elements needs more
+// registers or LDS already allows only a few blocks.
 template <int MAXB, int EC> constexpr int dec_waves_per_eu()
 {
-    return MAXB <= kSmallBlock && EC != 12 && EC != 16 ? 4 : 1;
+    if (EC == 12 || EC == 16) return 1;
+    return MAXB <= kTinyBlock ? 5 : MAXB <= kSmallBlock ? 4 : 1;
 }
 
 template <int MAXB> struct DecLds {

@@ -238,6 +238,23 @@ def test_compress_many_sequences(bsg, E, nb):
     assert np.array_equal(back[: n * E], data)
 
 
+@pytest.mark.parametrize("E", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("block_bytes", [2048, 4096, 4224, 8192, 8320, 16384, 16512, 32768, 65536])
+def test_compress_block_sizes(bsg, E, block_bytes):
+    """Blocks at the edges of the kernels' block sizes, of a random walk (in
+    the transposed domain: constant planes, noise and short matches) and of
+    incompressible bytes, with a short last block."""
+    nb = block_bytes // E // 8 * 8
+    n = 2 * nb + nb // 16 * 8 + 3
+    walk = synth.gen_walk_int16(n * E // 2 + 1, block_bytes + E).view(np.uint8)[: n * E].copy()
+    noise = synth.gen_uniform_bytes(n * E, E)
+    for data in (walk, noise):
+        ref = oracle.compress(data, E, nb)
+        got = host(bsg.compress_sync(dev(data), E, nb))
+        assert got.size == ref.size and np.array_equal(got, ref)
+        assert np.array_equal(host(bsg.decompress_sync(dev(ref), n, E, nb))[: n * E], data)
+
+
 @pytest.mark.parametrize("lit_max", [1, 3, 9, 40, 300])
 def test_compress_literal_runs(bsg, lit_max):
     """Literal runs of 0 .. lit_max bytes at every alignment (the copies of a
