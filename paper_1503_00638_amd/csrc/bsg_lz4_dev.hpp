@@ -1130,10 +1130,9 @@ template <int MAXB> struct DecLds {
 
 // Stage the LZ4 bytes of block b of a stream (payload / off as laid out in
 // the stream) at the tail of the in-place buffer B (B[-1] readable padding)
-// with the same 4-byte phase as in HBM: the 16-byte lines holding them, one
-// per lane and step (the dwords before the block land in the free output
-// space, the last line's bytes past it in the padding; a line past in_end
-// is read byte by byte).  Returns false when the block's offsets are not
+// with the same 4-byte phase as in HBM: the 16-byte lines holding them (the
+// dwords before the block land in the free output space, the last line's
+// bytes past it in the padding; of a line past in_end the bytes before it).  Returns false when the block's offsets are not
 // plausible; else base / len: where the bytes start in B and how many.
 template <int MAXB>
 __device__ __forceinline__ bool stage_lz4(const uint8_t *__restrict__ payload, int64_t payload_len,
@@ -1153,22 +1152,37 @@ __device__ __forceinline__ bool stage_lz4(const uint8_t *__restrict__ payload, i
     const uint4 *s128 = reinterpret_cast<const uint4 *>(src - s16);
     const int lines = (s16 + len + 15) >> 4;
     const int d0 = w0 - ((s16 - s) >> 2);      // buffer dword of the first line's first dword
-    for (int k = lane; k < lines; k += kWave) {
-        const uint8_t *lp = reinterpret_cast<const uint8_t *>(s128 + k);
-        uint4 v;
-        if (lp + 16 <= in_end) {
-            v = s128[k];
-        } else {
-            uint32_t x[4] = {0, 0, 0, 0};
-            for (int j = 0; j < 16; ++j)
-                if (lp + j < in_end) x[j >> 2] |= (uint32_t)lp[j] << (8 * (j & 3));
-            v = make_uint4(x[0], x[1], x[2], x[3]);
+    uint32_t *d = B + d0;
+    // whole lines (all but the stream's last one): all loads of a step (4
+    // KiB) before its first write (one line per lane and round trip took
+    // 1.10 ms for the 2.16 GB chunk, this takes 1.02)
+    const int whole = reinterpret_cast<const uint8_t *>(s128 + lines) <= in_end ? lines : lines - 1;
+    constexpr int kSteps = 4;
+    for (int k0 = 0; k0 < whole; k0 += kSteps * kWave) {
+        uint4 v[kSteps];
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) {
+            const int k = k0 + j * kWave + lane;
+            if (k < whole) v[j] = s128[k];
         }
-        uint32_t *d = B + d0 + 4 * k;
-        d[0] = v.x;
-        d[1] = v.y;
-        d[2] = v.z;
-        d[3] = v.w;
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) {
+            const int k = k0 + j * kWave + lane;
+            if (k < whole) {
+                d[4 * k] = v[j].x;
+                d[4 * k + 1] = v[j].y;
+                d[4 * k + 2] = v[j].z;
+                d[4 * k + 3] = v[j].w;
+            }
+        }
+    }
+    if (whole < lines && lane < 4) { // a dword per lane, nothing read past in_end
+        const uint8_t *p = reinterpret_cast<const uint8_t *>(s128 + whole) + 4 * lane;
+        uint32_t x = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (p + i < in_end) x |= (uint32_t)p[i] << (8 * i);
+        d[4 * whole + lane] = x;
     }
     return true;
 }
