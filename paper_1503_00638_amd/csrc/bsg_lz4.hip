@@ -13,8 +13,6 @@
 // copy by HBM).
 // Decompression = k_decode (stage the LZ4 block in LDS, decode into LDS,
 // inverse transpose on the way out to HBM).
-#include <type_traits>
-
 #include "bsg_lz4_dev.hpp"
 
 namespace bsg {
@@ -123,11 +121,7 @@ __global__ __launch_bounds__(64) void k_offsets(PackArgs a)
     int64_t before = 0;
 #pragma unroll 4
     for (int64_t k = lane; k < tile; k += kWave) before += a.tile_sum[k];
-    // the lanes' 64-bit sums added up in two parts of 24 bits and the rest
-    int lo, hi;
-    wave_excl_scan((int)(before & 0xFFFFFF), lo);
-    wave_excl_scan((int)(before >> 24), hi);
-    int64_t base = ((int64_t)hi << 24) + lo;
+    int64_t base = wave_sum_i64(before);
     uint64_t *off = offsets_of(a);
 #pragma unroll
     for (int s = 0; s < kTile / kStrip; ++s) {
@@ -326,15 +320,6 @@ hipError_t decode_dispatch(const DecArgs &a, int ec, hipStream_t s)
     }
 }
 
-// f(the smallest instance's block size that holds blocks of this many bytes).
-template <typename F> auto for_block_size(int64_t bytes, F f)
-{
-    if (bytes <= kTinyBlock) return f(std::integral_constant<int, kTinyBlock>{});
-    if (bytes <= kSmallBlock) return f(std::integral_constant<int, kSmallBlock>{});
-    if (bytes <= kMidBlock) return f(std::integral_constant<int, kMidBlock>{});
-    return f(std::integral_constant<int, kLargeBlock>{});
-}
-
 } // namespace
 
 int64_t compress_workspace(const Layout &L)
@@ -354,7 +339,8 @@ int64_t compress_workspace(const Layout &L)
 // of the count.
 constexpr int64_t kSelfMaxBlocks = 4096;
 
-constexpr int kMaxSeg = kSideEvents;     // segments of a large input
+constexpr int kMaxSeg = 16;             // segments of a large input
+static_assert(kMaxSeg <= kSideEvents, "an event per segment");
 constexpr int64_t kSegMinBlocks = 8192; // ... of at least this many blocks
 // Segments pay only when the encoder leaves registers for the pack waves
 // beside its 4 resident waves per SIMD (LDS allows 16 per CU): at 112 VGPRs

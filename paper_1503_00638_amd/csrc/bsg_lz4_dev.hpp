@@ -4,6 +4,8 @@
 // gfx950 a block lives in LDS and one wavefront owns it.
 #pragma once
 
+#include <type_traits>
+
 #include "bsg_internal.hpp"
 #include "bsg_round_dev.hpp"
 #include "bsg_shuffle_dev.hpp"
@@ -12,9 +14,7 @@ namespace bsg {
 namespace {
 
 
-// Block sizes the kernels have instances for: the batched ones for the default
-// block and the largest, the single-stream ones for two more.  The LDS of a
-// workgroup, and so the blocks in flight on a CU, follows the instance (the
+// Block sizes the kernels have instances for.  The LDS of a workgroup, and so the blocks in flight on a CU, follows the instance (the
 // encoder's 26, 16, 8 and 2; the decoder's 36, 18, 9 and 2): 4 KiB blocks
 // encoded at 89 us in the 8 KiB instance and 83 in their own (65 MB of 8-byte
 // elements), 16 KiB ones ran 2.7 times as long in the 64 KiB instance.
@@ -154,6 +154,13 @@ __device__ __forceinline__ void block_forward_ballot_round(const uint8_t *__rest
 // k * elems + i.
 constexpr int kByteShuffle = -1;
 
+// Element class of the batched kernels that take blocks of 1-, 2-, 4- and
+// 8-byte elements and of sizes without a register path in one launch: the
+// block's own element size picks its staging (a wave-uniform branch).  Their
+// register needs lie below what LDS lets reside anyway; 12- and 16-byte
+// elements need more and stay apart.
+constexpr int kMixed = -2;
+
 // Lanes take 4 elements at a time, so every LDS access is one aligned dword
 // (elems is a multiple of 8).
 // Byte shuffle of elements whose size is a multiple of 4 (E <= 16), the
@@ -273,6 +280,14 @@ __device__ __forceinline__ void stage_block(const uint8_t *__restrict__ src, int
             block_forward_ballot_round(src, lds, elems, rp, first_elem);
     } else if constexpr (EC == kByteShuffle) {
         block_forward_bytes(src, lds, elems, E);
+    } else if constexpr (EC == kMixed) {
+        switch (E) {
+        case 1: stage_block<1, RM>(src, elems, E, lds, rp, first_elem); break;
+        case 2: stage_block<2, RM>(src, elems, E, lds, rp, first_elem); break;
+        case 4: stage_block<4, RM>(src, elems, E, lds, rp, first_elem); break;
+        case 8: stage_block<8, RM>(src, elems, E, lds, rp, first_elem); break;
+        default: stage_block<0, RM>(src, elems, E, lds, rp, first_elem); break;
+        }
     } else {
         if constexpr (EC != 0) {
             if (elems % Unit<EC>::G == 0 && ((uintptr_t)src % 16) == 0) {
@@ -668,19 +683,14 @@ __device__ __forceinline__ int encode_block(const uint32_t *b32, int n, uint32_t
 }
 
 // ---- sizes -> offsets -------------------------------------------------------
-__device__ __forceinline__ int64_t block_sum_i64(int64_t v, int64_t *sh)
+// Sum of x (0 <= x < 2^48) over the wave's lanes, in two parts of 24 bits and
+// the rest.
+__device__ __forceinline__ int64_t wave_sum_i64(int64_t x)
 {
-    // 256-thread inclusive scan helper storage: sh[256]
-    const int t = threadIdx.x;
-    sh[t] = v;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        const int64_t x = t >= o ? sh[t - o] : 0;
-        __syncthreads();
-        sh[t] += x;
-        __syncthreads();
-    }
-    return sh[t]; // inclusive
+    int lo, hi;
+    wave_excl_scan((int)(x & 0xFFFFFF), lo);
+    wave_excl_scan((int)(x >> 24), hi);
+    return ((int64_t)hi << 24) + lo;
 }
 
 __device__ __forceinline__ void fail(int32_t *status)
@@ -1027,6 +1037,31 @@ __device__ __forceinline__ void unstage_block(const uint8_t *lds, int64_t elems,
     block_inverse_bits(lds, dst, elems, E);
 }
 
+// unstage_block, with the element count a constant for full blocks.
+template <int MAXB, int EC>
+__device__ __forceinline__ void unstage_any(const uint8_t *lds, int64_t elems, int64_t E,
+                                            uint8_t *__restrict__ dst, bool fast_out)
+{
+    if constexpr (EC == kMixed) {
+        switch (E) {
+        case 1: unstage_any<MAXB, 1>(lds, elems, E, dst, fast_out); return;
+        case 2: unstage_any<MAXB, 2>(lds, elems, E, dst, fast_out); return;
+        case 4: unstage_any<MAXB, 4>(lds, elems, E, dst, fast_out); return;
+        case 8: unstage_any<MAXB, 8>(lds, elems, E, dst, fast_out); return;
+        default: unstage_any<MAXB, 0>(lds, elems, E, dst, fast_out); return;
+        }
+    } else {
+        constexpr int64_t kFull = full_block_elems<MAXB, EC>();
+        if constexpr (kFull != 0) {
+            if (fast_out && elems == kFull) {
+                unstage_fast<EC>(lds, kFull, dst);
+                return;
+            }
+        }
+        unstage_block<EC>(lds, elems, E, dst, fast_out);
+    }
+}
+
 // Bytes of the in-place LDS buffer for blocks up to MAXB bytes: the block
 // plus the slack a valid LZ4 block needs so that output never overtakes
 // unread input (any suffix of a block codes its output with at most
@@ -1119,7 +1154,7 @@ __device__ __forceinline__ int encode_one(const uint8_t *__restrict__ src, int64
 template <int MAXB, int EC> constexpr int dec_waves_per_eu()
 {
     if (EC == 12 || EC == 16) return 1;
-    return MAXB <= kTinyBlock ? 5 : MAXB <= kSmallBlock ? 4 : 1;
+    return MAXB <= kTinyBlock && EC != kMixed ? 5 : MAXB <= kSmallBlock ? 4 : 1;
 }
 
 template <int MAXB> struct DecLds {
@@ -1209,16 +1244,7 @@ __device__ __forceinline__ bool decode_one(const uint8_t *__restrict__ payload, 
     __builtin_amdgcn_s_setprio(0);
     wave_sync();
     if (ok) {
-        constexpr int64_t kFull = full_block_elems<MAXB, EC>();
-        bool done = false;
-        if constexpr (kFull != 0) {
-            if (fast_out && elems == kFull) {
-                unstage_fast<EC>(reinterpret_cast<const uint8_t *>(B), kFull, dst);
-                done = true;
-            }
-        }
-        if (!done)
-            unstage_block<EC>(reinterpret_cast<const uint8_t *>(B), elems, E, dst, fast_out);
+        unstage_any<MAXB, EC>(reinterpret_cast<const uint8_t *>(B), elems, E, dst, fast_out);
     }
     wave_sync();
     return ok;
@@ -1235,6 +1261,15 @@ __device__ __forceinline__ bool header_ok(const uint8_t *in, int64_t payload_len
     return h->magic == magic && h->elem_size == (uint32_t)E && h->n == (uint64_t)n &&
            h->block_elems == (uint32_t)nb && h->n_blocks == (uint32_t)n_blocks && off[0] == 0 &&
            off[n_blocks] == (uint64_t)payload_len;
+}
+
+// f(the smallest instance's block size that holds blocks of this many bytes).
+template <typename F> auto for_block_size(int64_t bytes, F f)
+{
+    if (bytes <= kTinyBlock) return f(std::integral_constant<int, kTinyBlock>{});
+    if (bytes <= kSmallBlock) return f(std::integral_constant<int, kSmallBlock>{});
+    if (bytes <= kMidBlock) return f(std::integral_constant<int, kMidBlock>{});
+    return f(std::integral_constant<int, kLargeBlock>{});
 }
 
 // The element class with a register fast path, or 0.

@@ -84,6 +84,37 @@ def test_batch_compress_and_decompress_parity(bsg):
         assert np.array_equal(host(dplan.outs[k])[: d.size], d), k
 
 
+@pytest.mark.parametrize("blocks", [900, 2500])
+def test_batch_split_classes(bsg, blocks):
+    """Classes that are split where they hold enough blocks (2500) or not
+    (900): all element sizes in one class, 12- and 16-byte ones apart, every
+    instance block size, chunks without a block at a class's ends; one chunk
+    one byte short of its stream."""
+    specs = [(E, 128 // E // 8 * 8, 128 // E // 8 * 8 * (blocks + 7 * E) + E % 5)
+             for E in (1, 2, 4, 8, 1, 2, 4, 8, 3, 5) for _ in (0, 1)]
+    specs += [(12, 16, 16 * 300 + 3), (16, 8, 8 * 200), (4, 2048, 2048 * 3 + 9), (4, 1024, 5000),
+              (2, 8192, 9000), (8, 8192, 8192 + 16), (4, 16, 0), (4, 16, 7), (16, 16, 3)]
+    data = [chunk_data(k, E, n) for k, (E, _, n) in enumerate(specs)]
+    Es, Bs = [E for E, _, _ in specs], [b for _, b, _ in specs]
+    refs = [oracle.compress(d, E, B) for d, E, B in zip(data, Es, Bs)]
+    outs = [torch.full((r.size,), 0xA5, dtype=torch.uint8, device="cuda:0") for r in refs]
+    short = 3
+    outs[short] = outs[short][: refs[short].size - 1]
+    plan = bsg.BatchPlan.for_compress([to_dev(d) for d in data], Es, Bs, outs=outs)
+    nb = host(plan.compress())
+    for k, ref in enumerate(refs):
+        if k == short:
+            assert nb[k] == bsg.BSG_ECAPACITY and (host(outs[k]) == 0xA5).all()
+        else:
+            assert nb[k] == ref.size and np.array_equal(host(outs[k]), ref), k
+    streams = [dev(r) for r in refs]
+    ns = [n for _, _, n in specs]
+    dplan = bsg.BatchPlan.for_decompress(streams, [r.size for r in refs], ns, Es, Bs)
+    assert not host(dplan.decompress()).any()
+    for k, d in enumerate(data):
+        assert np.array_equal(host(dplan.outs[k])[: d.size], d), k
+
+
 def test_batch_launch_shape_does_not_change_bytes(bsg):
     data, Es, Bs = mixed()
     xs = [to_dev(d) for d in data]
