@@ -11,6 +11,8 @@
 // The value is scaled by 2^-k in double, rounded half to even there and
 // scaled back (both scalings exact); k comes from the exponent and mantissa
 // of the double G2 (frexp): no log, sqrt or division.
+#include <algorithm>
+
 #include "bsg_internal.hpp"
 #include "bsg_round_dev.hpp"
 
@@ -129,93 +131,151 @@ __global__ __launch_bounds__(256) void k_round_i32(const int2 *__restrict__ vin,
 // Compensation of the diagonal noise model (Section 3.2): per (frequency,
 // time) the minimum over cross products of 1 - |V_ij|^2 / (V_ii V_jj), in
 // double and in that order (products with V_ii V_jj not positive and finite
-// skipped, 1 when none is left).  A workgroup takes one frequency and 64
-// times; its 4 wavefronts walk a quarter of the products each (lanes =
-// times, so every load is coalesced) and the 4 partial minima meet in LDS.
-__global__ __launch_bounds__(256) void k_noise_comp(const float2 *__restrict__ vis, RoundParams rp,
-                                                    double *__restrict__ scale)
+// skipped, 1 when none is left).  A workgroup of 512 threads takes Tb <= 512
+// times and up to kCompPairs products, of one frequency after the other:
+// thread k takes time k mod Tb and every R-th product from k / Tb (R = 512 /
+// Tb), so each step of the workgroup reads about 4 KiB of the contiguous
+// [P][T] block.  The places of a product's two autos come from a table in LDS
+// made once, the frequency's autos are in LDS too.  The per-thread minima
+// meet in LDS, those of several workgroups in an atomic minimum on the
+// output, set to 1 before.  The minimum does not depend on the order of the
+// terms (no term is -0, NaN terms are skipped).
+//
+// Bound by HBM reads.  A double-precision division per product and stepping
+// the inputs along took 70 instructions per product and kept it from there:
+// 201 us for 541 MB (256 frequencies, 128 inputs, 32 times), 541 us for 2.16
+// GB; now 129 and 436 us (5.0 TB/s), and times that are no power of two or
+// few frequencies no longer go to a slower kernel (2 frequencies, 512 inputs,
+// 30 times: 20.8 ms -> 30 us).  So a product is first screened
+// in float32 against the lowest term any thread has found for its time
+// (`best`): with q = |V_ij|^2, ab = V_ii V_jj and c = ab (1 - best)(1 -
+// 2^-18), all rounded to float32, q <= c with c finite and at least 1e-30
+// (where underflow in q is far below the margin) puts the exact quotient
+// below (1 - best)(1 - 2^-20), so the exact term, rounded, is not below
+// best.  Where that fails (products that lower the minimum, or without
+// a usable ab) the exact path follows, which is soon rare.
+constexpr int kCompThreads = 512;
+constexpr int kCompAhead = 8;       // visibilities a thread loads before it uses the first
+constexpr int kCompPairs = 8192;    // products a workgroup has a table for (32 KiB)
+constexpr int kCompAutos = 16384;   // autos of one frequency and Tb times (64 KiB)
+
+// LDS: i Tb and j Tb of the workgroup's products fit 16 bits each and the
+// autos their place; else (more inputs than kCompAutos) both are found again
+// for each product.
+template <bool LDS>
+__global__ __launch_bounds__(kCompThreads) void k_noise_comp(const float2 *__restrict__ vis,
+                                                             RoundParams rp,
+                                                             double *__restrict__ scale, int Tb,
+                                                             int parts)
 {
-    __shared__ double part[4][kWave];
-    const int tl = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int64_t fr = blockIdx.x;
-    const int64_t t = int64_t(blockIdx.y) * kWave + tl;
-    double m = 1.0;
-    const int64_t p0 = rp.P * q / 4, p1 = rp.P * (q + 1) / 4;
-    if (t < rp.T && p0 < p1) {
-        VisCursor c = cursor_at(rp, (fr * rp.P + p0) * rp.T + t);
-        for (int64_t p = p0;;) {
-            if (c.i != c.j) {
-                const double ab = (double)rp.autos[c.row_i + c.t] * (double)rp.autos[c.row_j + c.t];
-                if (ab > 0.0 && ab != __builtin_inf()) {
-                    const float2 v = vis[(fr * rp.P + p) * rp.T + t];
-                    const double term =
-                        1.0 - ((double)v.x * (double)v.x + (double)v.y * (double)v.y) / ab;
-                    if (term < m) m = term; // a NaN term never wins
-                }
-            }
-            if (++p == p1) break;
-            cursor_next_product(rp, c);
+    __shared__ double part[kCompThreads];
+    __shared__ double best[kCompThreads]; // per time; many threads write it, any term found will do
+    extern __shared__ uint32_t dyn[];     // LDS: the products' table, then the autos
+    const int k = threadIdx.x;
+    const int R = kCompThreads / Tb, r = k / Tb, tl = k - r * Tb;
+    const int64_t T = rp.T, t0 = (int64_t)blockIdx.z * Tb, t = t0 + tl;
+    const int64_t per = (rp.P + parts - 1) / parts, first = per * blockIdx.y;
+    const int count = (int)(rp.P - first < per ? (rp.P > first ? rp.P - first : 0) : per);
+    uint32_t *pairs = dyn;
+    float *la = reinterpret_cast<float *>(dyn + per);
+    const bool mine = r < R && t < T;
+    if constexpr (LDS) {
+        for (int p = k; p < count; p += kCompThreads) {
+            int32_t i, j;
+            product_pair(rp, first + p, i, j);
+            pairs[p] = (uint32_t)(i * Tb) | (uint32_t)(j * Tb) << 16;
         }
     }
-    part[q][tl] = m;
-    __syncthreads();
-    if (q == 0 && t < rp.T) {
-        for (int k = 1; k < 4; ++k)
-            if (part[k][tl] < m) m = part[k][tl];
-        scale[fr * rp.T + t] = m;
+    for (int64_t fr = blockIdx.x; fr < rp.F; fr += gridDim.x) {
+        const float2 *vbase = vis + (fr * rp.P + first) * T;
+        const float *abase = rp.autos + fr * rp.I * T;
+        if constexpr (LDS) {
+            for (int e = k; e < (int)rp.I * Tb; e += kCompThreads) {
+                const int i = e / Tb;
+                const int64_t ta = t0 + e - i * Tb;
+                la[e] = ta < T ? abase[i * T + ta] : 0.0f;
+            }
+        }
+        best[k] = 1.0;
+        __syncthreads();
+        double m = 1.0;
+        // the autos of product p of the workgroup; false for an auto product
+        const auto autos_of = [&](int p, float &ai, float &aj) {
+            if constexpr (LDS) {
+                const uint32_t x = pairs[p], a = x & 0xFFFFu, b = x >> 16;
+                ai = la[a + tl];
+                aj = la[b + tl];
+                return a != b;
+            } else {
+                int32_t i, j;
+                product_pair(rp, first + p, i, j);
+                ai = abase[i * T + t];
+                aj = abase[j * T + t];
+                return i != j;
+            }
+        };
+        const int64_t mine0 = r * T + t;
+        const auto exact_term = [&](float2 v, float ai, float aj) {
+            const double ab = (double)ai * (double)aj;
+            const double term = 1.0 - ((double)v.x * (double)v.x + (double)v.y * (double)v.y) / ab;
+            // a NaN term never wins
+            if (ab > 0.0 && ab != __builtin_inf() && term < m) m = term;
+        };
+        if (mine) {
+            int p = 0; // uniform; the thread's product is p + r
+            for (; p + kCompAhead * R <= count; p += kCompAhead * R) {
+                float2 v[kCompAhead];
+#pragma unroll
+                for (int u = 0; u < kCompAhead; ++u) v[u] = vbase[(int64_t)(p + u * R) * T + mine0];
+                const double b = __hip_atomic_load(&best[tl], __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                const float thr = (float)((1.0 - b) * (1.0 - 0x1p-18));
+                float ai[kCompAhead], aj[kCompAhead];
+                bool need[kCompAhead], any = false;
+#pragma unroll
+                for (int u = 0; u < kCompAhead; ++u) {
+                    const bool cross = autos_of(p + u * R + r, ai[u], aj[u]);
+                    const float q = v[u].x * v[u].x + v[u].y * v[u].y, ab = ai[u] * aj[u];
+                    const float c = thr * ab;
+                    need[u] = cross && !(q <= c && c >= 1e-30f && c < __builtin_inff());
+                    any |= need[u];
+                }
+                if (any) {
+#pragma unroll
+                    for (int u = 0; u < kCompAhead; ++u)
+                        if (need[u]) exact_term(v[u], ai[u], aj[u]);
+                    if (m < b)
+                        __hip_atomic_store(&best[tl], m, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+            for (; p + r < count; p += R) {
+                float ai, aj;
+                if (autos_of(p + r, ai, aj)) exact_term(vbase[p * T + mine0], ai, aj);
+            }
+        }
+        part[k] = m;
+        __syncthreads();
+        for (int n = R; n > 1;) { // rows r < n hold minima: fold the upper half
+            const int h = (n + 1) / 2;
+            if (r < n - h && part[k + h * Tb] < part[k]) part[k] = part[k + h * Tb];
+            n = h;
+            __syncthreads();
+        }
+        if (r == 0 && t < T) {
+            if (parts == 1)
+                scale[fr * T + t] = part[k];
+            else if (part[k] < 1.0)
+                atomicMin(&scale[fr * T + t], part[k]);
+        }
+        __syncthreads();
     }
 }
 
-// T a power of two up to 1024: one workgroup of 1024 threads per frequency.
-// Thread k takes time t = k mod T and the products p = k / T, k / T + R, ...
-// (R = 1024 / T), so each step of the workgroup reads 8 KiB of the
-// contiguous [P][T] block of that frequency; the thread's inputs (i, j) are
-// stepped along with p.  The per-thread minima are then reduced over the R
-// threads of each time in LDS.  The minimum does not depend on the order of
-// the terms (no term is -0, NaN terms are skipped).
-constexpr int kCompThreads = 1024;
-
-__global__ __launch_bounds__(kCompThreads) void k_noise_comp_rows(const float2 *__restrict__ vis,
-                                                                 RoundParams rp,
-                                                                 double *__restrict__ scale)
+__global__ __launch_bounds__(256) void k_ones(double *__restrict__ out, int64_t n)
 {
-    __shared__ double part[kCompThreads];
-    const int k = threadIdx.x;
-    const int T = (int)rp.T, R = kCompThreads / T;
-    const int t = k & (T - 1), r = k / T;
-    const int64_t fr = blockIdx.x;
-    const float2 *vrow = vis + fr * rp.P * rp.T + t;
-    const float *arow = rp.autos + fr * rp.I * rp.T + t;
-    double m = 1.0;
-    int32_t i = 0, j = 0;
-    if (r < rp.P) product_pair(rp, r, i, j);
-#pragma unroll 4
-    for (int64_t p = r; p < rp.P; p += R) {
-        const float2 v = vrow[p * T];
-        const double ab = (double)arow[(int64_t)i * T] * (double)arow[(int64_t)j * T];
-        const double term = 1.0 - ((double)v.x * (double)v.x + (double)v.y * (double)v.y) / ab;
-        if (i != j && ab > 0.0 && ab != __builtin_inf() && term < m) m = term; // a NaN term never wins
-        // the inputs of product p + R
-        if (rp.prod_map) {
-            if (p + R < rp.P) {
-                i = rp.prod_map[2 * (p + R)];
-                j = rp.prod_map[2 * (p + R) + 1];
-            }
-        } else {
-            j += R;
-            while (j >= rp.I && i < rp.I) {
-                j += i + 1 - (int32_t)rp.I; // the next row starts at j = i + 1
-                ++i;
-            }
-        }
-    }
-    part[k] = m;
-    __syncthreads();
-    for (int st = R / 2; st >= 1; st >>= 1) {
-        if (r < st && part[k + st * T] < part[k]) part[k] = part[k + st * T];
-        __syncthreads();
-    }
-    if (r == 0) scale[fr * T + t] = part[t];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        out[i] = 1.0;
 }
 
 } // namespace
@@ -248,15 +308,35 @@ hipError_t launch_round_i32(const int32_t *vin, int32_t *vout, const RoundParams
 
 hipError_t launch_noise_comp(const float *vis, const RoundParams &rp, double *scale, hipStream_t s)
 {
-    if (rp.F * rp.T == 0) return hipSuccess;
-    if (rp.T <= kCompThreads && (rp.T & (rp.T - 1)) == 0) {
-        hipLaunchKernelGGL(k_noise_comp_rows, dim3((unsigned)rp.F), dim3(kCompThreads), 0, s,
-                           reinterpret_cast<const float2 *>(vis), rp, scale);
-        return hipGetLastError();
+    const int64_t n = rp.F * rp.T;
+    if (n == 0) return hipSuccess;
+    const bool lds = rp.I <= kCompAutos;
+    const int64_t fit = lds ? kCompAutos / std::max<int64_t>(rp.I, 1) : kCompThreads;
+    const int Tb = (int)std::min<int64_t>({rp.T, kCompThreads, fit});
+    const int64_t tiles = (rp.T + Tb - 1) / Tb;
+    // Enough parts for three workgroups per CU (as many as reside), if each
+    // keeps four steps, and for the table.
+    const int64_t steps = rp.P / (kCompAhead * (kCompThreads / Tb));
+    const int parts = (int)std::max<int64_t>(
+        {(rp.P + kCompPairs - 1) / kCompPairs, 1,
+         std::min<int64_t>(steps / 4, (3 * 256 + rp.F * tiles - 1) / (rp.F * tiles))});
+    if (parts > 1) {
+        hipLaunchKernelGGL(k_ones, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256),
+                           0, s, scale, n);
+        if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    const dim3 grid((unsigned)rp.F, (unsigned)((rp.T + kWave - 1) / kWave));
-    hipLaunchKernelGGL(k_noise_comp, grid, dim3(256), 0, s, reinterpret_cast<const float2 *>(vis),
-                       rp, scale);
+    // workgroups of the same products take further frequencies past eight per CU
+    const int64_t gx = std::min<int64_t>(rp.F, std::max<int64_t>(1, 8 * 256 / (parts * tiles)));
+    const dim3 grid((unsigned)gx, (unsigned)parts, (unsigned)tiles);
+    const int64_t per = (rp.P + parts - 1) / parts;
+    const size_t dyn = lds ? 4 * (size_t)(per + rp.I * Tb) : 0;
+    const float2 *v = reinterpret_cast<const float2 *>(vis);
+    if (lds)
+        hipLaunchKernelGGL((k_noise_comp<true>), grid, dim3(kCompThreads), dyn, s, v, rp, scale, Tb,
+                           parts);
+    else
+        hipLaunchKernelGGL((k_noise_comp<false>), grid, dim3(kCompThreads), 0, s, v, rp, scale, Tb,
+                           parts);
     return hipGetLastError();
 }
 

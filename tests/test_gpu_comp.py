@@ -75,6 +75,32 @@ def test_compensation_degenerate_inputs(bsg, T):
     assert np.array_equal(got_r.view(np.uint32), ref_r.view(np.uint32))
 
 
+@pytest.mark.parametrize("F,I,T", [(1, 128, 32), (2, 40, 1), (3, 12, 513), (1, 9, 1100), (2, 61, 50),
+                                   (1, 200, 7), (600, 3, 5)])
+def test_compensation_shapes_and_scales(bsg, F, I, T):
+    """Products over several workgroups, times of every kind, and a float32
+    screening that has to let every product through that matters: autos and
+    visibilities over 60 decades (products that overflow or underflow in
+    float32), correlations of nearly 1, repeated minima, zero, negative,
+    infinite and NaN values."""
+    rng = np.random.default_rng(F * 1000 + I + T)
+    vis, autos = synth.gen_vis_point_source(F, I, T, 5, 0.4)
+    g = (10.0 ** rng.uniform(-15, 15, (F, I, T))).astype(np.float32)
+    pairs = synth.product_pairs(I)
+    with np.errstate(over="ignore", under="ignore", invalid="ignore"):
+        vis = (vis * np.sqrt(g[:, pairs[:, 0]]) * np.sqrt(g[:, pairs[:, 1]])).astype(np.complex64)
+        autos = (autos * g).astype(np.float32)
+    flat = autos.reshape(-1)
+    for v in (0.0, -1.0, np.inf, np.nan, 1e38, 1e-40):
+        flat[rng.integers(0, flat.size, max(1, flat.size // 97))] = v
+    vflat = vis.view(np.float32).reshape(-1)
+    for v in (0.0, np.inf, np.nan, 1e38, 1e-40):
+        vflat[rng.integers(0, vflat.size, max(1, vflat.size // 199))] = v
+    ref = oracle.noise_compensation(vis, autos)
+    got = host(bsg.noise_compensation(dev(vis), dev(autos)))
+    assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
+
+
 def test_unit_scale_is_plain_rounding(bsg):
     vis, autos = synth.gen_vis(4, 8, 64, 0)
     ones = torch.ones((4, 64), dtype=torch.float64, device="cuda:0")
