@@ -22,109 +22,117 @@ namespace {
 
 constexpr int kComplexPerThread = 4;
 
-// Lane i of the grid rounds the kComplexPerThread consecutive visibilities
-// from e0 = i * kComplexPerThread.  When they lie in one product row at one
-// frequency (times t .. t + 3, the case whenever T is a multiple of 4), the
-// values and their autos are read with 16-byte loads from one base each and
-// every value is rounded without a branch; otherwise a cursor steps through
-// them one by one.
-__global__ __launch_bounds__(256) void k_round(const float2 *__restrict__ vin,
-                                               float2 *__restrict__ vout, RoundParams rp,
-                                               int64_t n_complex, int aligned16)
+// K visibilities of one or two rows (see RowRun), 16-byte aligned: values and
+// autos are all loaded before the first is rounded, without a branch.
+template <bool TWO>
+__device__ __forceinline__ void round_run(const float2 *__restrict__ vin, float2 *__restrict__ vout,
+                                          const RoundParams &rp, const VisCursor &c)
 {
     constexpr int K = kComplexPerThread;
-    const int64_t e0 = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) * K;
-    if (e0 >= n_complex) return;
-    VisCursor c = cursor_at(rp, e0);
-    if (aligned16 && e0 + K <= n_complex && c.t + K <= rp.T) {
-        const float4 *v4 = reinterpret_cast<const float4 *>(vin + e0);
-        float4 v[K / 2];
+    const float4 *v4 = reinterpret_cast<const float4 *>(vin);
+    float4 v[K / 2];
 #pragma unroll
-        for (int k = 0; k < K / 2; ++k) v[k] = v4[k];
-        const float *pi = rp.autos + c.row_i + c.t;
-        const float *pj = rp.autos + c.row_j + c.t;
-        float ai[K], aj[K];
-        double sc[K];
+    for (int k = 0; k < K / 2; ++k) v[k] = v4[k];
+    const RowRun<K, TWO, float> row(rp, c, rp.autos);
+    float ai[K], aj[K];
+    double sc[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            ai[k] = pi[k];
-            aj[k] = pj[k];
-            sc[k] = 1.0;
-        }
-        if (rp.fscale) {
-            const double *fs = rp.fscale + c.fr * rp.T + c.t;
-#pragma unroll
-            for (int k = 0; k < K; ++k) sc[k] = fs[k];
-        }
-        const bool is_auto = c.i == c.j;
-        float4 *o4 = reinterpret_cast<float4 *>(vout + e0);
-#pragma unroll
-        for (int k = 0; k < K / 2; ++k) {
-            uint32_t x[4] = {__float_as_uint(v[k].x), __float_as_uint(v[k].y), __float_as_uint(v[k].z),
-                             __float_as_uint(v[k].w)};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int j = 2 * k + h;
-                double G2 = ((double)ai[j] * (double)aj[j]) * (is_auto ? rp.c_auto : rp.c);
-                if (rp.fscale) G2 *= sc[j];
-                x[2 * h] = round_noise_bits_nb(x[2 * h], G2);
-                if (!is_auto) x[2 * h + 1] = round_noise_bits_nb(x[2 * h + 1], G2);
-            }
-            o4[k] = make_float4(__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]),
-                                __uint_as_float(x[3]));
-        }
-        return;
+    for (int k = 0; k < K; ++k) {
+        ai[k] = row.ai(k);
+        aj[k] = row.aj(k);
+        sc[k] = 1.0;
     }
-    for (int k = 0; k < K && e0 + k < n_complex; ++k) {
-        if (k) cursor_advance(rp, c, 1);
-        vout[e0 + k] = round_at(vin[e0 + k], c, rp);
+    if (rp.fscale) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) sc[k] = row.factor(k);
+    }
+    float4 *o4 = reinterpret_cast<float4 *>(vout);
+#pragma unroll
+    for (int k = 0; k < K / 2; ++k) {
+        uint32_t x[4] = {__float_as_uint(v[k].x), __float_as_uint(v[k].y), __float_as_uint(v[k].z),
+                         __float_as_uint(v[k].w)};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int j = 2 * k + h;
+            const bool is_auto = row.is_auto(j);
+            double G2 = ((double)ai[j] * (double)aj[j]) * (is_auto ? rp.c_auto : rp.c);
+            if (rp.fscale) G2 *= sc[j];
+            x[2 * h] = round_noise_bits_nb(x[2 * h], G2);
+            if (!is_auto) x[2 * h + 1] = round_noise_bits_nb(x[2 * h + 1], G2);
+        }
+        o4[k] = make_float4(__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]),
+                            __uint_as_float(x[3]));
     }
 }
 
-// As k_round, for int32 visibilities and autos (exact int64 products).
-__global__ __launch_bounds__(256) void k_round_i32(const int2 *__restrict__ vin,
-                                                   int2 *__restrict__ vout, RoundParams rp,
-                                                   int64_t n_complex, int aligned16)
+// As round_run, for int32 visibilities and autos (exact int64 products).
+template <bool TWO>
+__device__ __forceinline__ void round_run(const int2 *__restrict__ vin, int2 *__restrict__ vout,
+                                          const RoundParams &rp, const VisCursor &c)
+{
+    constexpr int K = kComplexPerThread;
+    const int4 *v4 = reinterpret_cast<const int4 *>(vin);
+    int4 v[K / 2];
+#pragma unroll
+    for (int k = 0; k < K / 2; ++k) v[k] = v4[k];
+    const RowRun<K, TWO, int32_t> row(rp, c, rp.autos_i32);
+    int64_t ai[K], aj[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        ai[k] = row.ai(k);
+        aj[k] = row.aj(k);
+    }
+    int4 *o4 = reinterpret_cast<int4 *>(vout);
+#pragma unroll
+    for (int k = 0; k < K / 2; ++k) {
+        int32_t x[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int j = 2 * k + h;
+            const bool is_auto = row.is_auto(j);
+            const double G2 = (double)(ai[j] * aj[j]) * (is_auto ? rp.c_auto : rp.c);
+            // (no estimate: k = 0, which changes nothing)
+            const int kk = G2 > 0.0 && G2 != __builtin_inf() ? granularity_k(G2) : 0;
+            x[2 * h] = round_int(x[2 * h], kk);
+            x[2 * h + 1] = round_int(x[2 * h + 1], is_auto ? 0 : kk);
+        }
+        o4[k] = make_int4(x[0], x[1], x[2], x[3]);
+    }
+}
+
+__device__ __forceinline__ float2 round_one(float2 v, const VisCursor &c, const RoundParams &rp)
+{
+    return round_at(v, c, rp);
+}
+__device__ __forceinline__ int2 round_one(int2 v, const VisCursor &c, const RoundParams &rp)
+{
+    return round_at_i32(v, c, rp);
+}
+
+// Lane i of the grid rounds the kComplexPerThread consecutive visibilities
+// from e0 = i * kComplexPerThread: a run of one row where T is a multiple of
+// 4, of two where T is at least 4; else (and at the array's end, or for
+// unaligned buffers) a cursor steps through them one by one.  (In two rows
+// every lane takes both bases.  Stepping was 42 us for 64 MB of integers at
+// 30 times, this is 28: HBM.)
+template <typename V2>
+__global__ __launch_bounds__(256) void k_round(const V2 *__restrict__ vin, V2 *__restrict__ vout,
+                                               RoundParams rp, int64_t n_complex, int aligned16)
 {
     constexpr int K = kComplexPerThread;
     const int64_t e0 = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) * K;
     if (e0 >= n_complex) return;
     VisCursor c = cursor_at(rp, e0);
-    if (aligned16 && e0 + K <= n_complex && c.t + K <= rp.T) {
-        const int4 *v4 = reinterpret_cast<const int4 *>(vin + e0);
-        int4 v[K / 2];
-#pragma unroll
-        for (int k = 0; k < K / 2; ++k) v[k] = v4[k];
-        const int32_t *pi = rp.autos_i32 + c.row_i + c.t;
-        const int32_t *pj = rp.autos_i32 + c.row_j + c.t;
-        int64_t ai[K], aj[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            ai[k] = pi[k];
-            aj[k] = pj[k];
-        }
-        const bool is_auto = c.i == c.j;
-        int4 *o4 = reinterpret_cast<int4 *>(vout + e0);
-#pragma unroll
-        for (int k = 0; k < K / 2; ++k) {
-            int32_t x[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int j = 2 * k + h;
-                const double G2 = (double)(ai[j] * aj[j]) * (is_auto ? rp.c_auto : rp.c);
-                if (G2 > 0.0 && G2 != __builtin_inf()) {
-                    const int kk = granularity_k(G2);
-                    x[2 * h] = round_int(x[2 * h], kk);
-                    if (!is_auto) x[2 * h + 1] = round_int(x[2 * h + 1], kk);
-                }
-            }
-            o4[k] = make_int4(x[0], x[1], x[2], x[3]);
-        }
+    if (aligned16 && e0 + K <= n_complex && rp.T >= K) {
+        if (rp.T % K == 0)
+            round_run<false>(vin + e0, vout + e0, rp, c);
+        else
+            round_run<true>(vin + e0, vout + e0, rp, c);
         return;
     }
     for (int k = 0; k < K && e0 + k < n_complex; ++k) {
         if (k) cursor_advance(rp, c, 1);
-        vout[e0 + k] = round_at_i32(vin[e0 + k], c, rp);
+        vout[e0 + k] = round_one(vin[e0 + k], c, rp);
     }
 }
 
@@ -287,7 +295,7 @@ hipError_t launch_round(const float *vin, float *vout, const RoundParams &rp, hi
     const int64_t waves = (n_complex + kWave * kComplexPerThread - 1) / (kWave * kComplexPerThread);
     const int64_t blocks = (waves * kWave + 255) / 256;
     const int aligned16 = (((uintptr_t)vin | (uintptr_t)vout) & 15) == 0;
-    hipLaunchKernelGGL(k_round, dim3((unsigned)blocks), dim3(256), 0, s,
+    hipLaunchKernelGGL((k_round<float2>), dim3((unsigned)blocks), dim3(256), 0, s,
                        reinterpret_cast<const float2 *>(vin), reinterpret_cast<float2 *>(vout),
                        rp, n_complex, aligned16);
     return hipGetLastError();
@@ -300,7 +308,7 @@ hipError_t launch_round_i32(const int32_t *vin, int32_t *vout, const RoundParams
     const int64_t waves = (n_complex + kWave * kComplexPerThread - 1) / (kWave * kComplexPerThread);
     const int64_t blocks = (waves * kWave + 255) / 256;
     const int aligned16 = (((uintptr_t)vin | (uintptr_t)vout) & 15) == 0;
-    hipLaunchKernelGGL(k_round_i32, dim3((unsigned)blocks), dim3(256), 0, s,
+    hipLaunchKernelGGL((k_round<int2>), dim3((unsigned)blocks), dim3(256), 0, s,
                        reinterpret_cast<const int2 *>(vin), reinterpret_cast<int2 *>(vout), rp,
                        n_complex, aligned16);
     return hipGetLastError();

@@ -151,6 +151,45 @@ __device__ __forceinline__ void cursor_advance(const RoundParams &rp, VisCursor 
     }
 }
 
+// Places of the autos (element type A) and factors of K consecutive
+// visibilities from cursor c, K <= T, so in at most two rows: k < m lie in
+// c's row, the others in the next product's.  With TWO = false all lie in
+// c's row (T a multiple of K, and the first at a multiple of K).
+template <int K, bool TWO, typename A> struct RowRun {
+    const A *i1, *j1, *i2, *j2;
+    const double *f1, *f2;
+    bool auto1, auto2;
+    int m;
+
+    __device__ RowRun(const RoundParams &rp, const VisCursor &c, const A *autos)
+    {
+        i1 = autos + c.row_i + c.t;
+        j1 = autos + c.row_j + c.t;
+        f1 = rp.fscale ? rp.fscale + c.fr * rp.T + c.t : nullptr;
+        auto1 = c.i == c.j;
+        m = K;
+        if constexpr (TWO) {
+            i2 = i1;
+            j2 = j1;
+            f2 = f1;
+            auto2 = auto1;
+            if (rp.T - c.t < K) {
+                m = (int)(rp.T - c.t);
+                VisCursor d = c;
+                cursor_next_product(rp, d);
+                i2 = autos + d.row_i - m;
+                j2 = autos + d.row_j - m;
+                f2 = rp.fscale ? rp.fscale + d.fr * rp.T - m : nullptr;
+                auto2 = d.i == d.j;
+            }
+        }
+    }
+    __device__ A ai(int k) const { return TWO ? (k < m ? i1 : i2)[k] : i1[k]; }
+    __device__ A aj(int k) const { return TWO ? (k < m ? j1 : j2)[k] : j1[k]; }
+    __device__ double factor(int k) const { return TWO ? (k < m ? f1 : f2)[k] : f1[k]; }
+    __device__ bool is_auto(int k) const { return TWO ? (k < m ? auto1 : auto2) : auto1; }
+};
+
 __device__ __forceinline__ float2 round_at(float2 v, const VisCursor &c, const RoundParams &rp)
 {
     const float ai = rp.autos[c.row_i + c.t];
@@ -163,17 +202,18 @@ __device__ __forceinline__ float2 round_at(float2 v, const VisCursor &c, const R
 // multiple, in exact integer arithmetic; only k >= 1 changes an integer.  A
 // result above INT32_MAX becomes the largest multiple of 2^k that fits (the
 // negative side always fits: -2^31 is a multiple of every 2^k, k <= 31).
+// (In 32-bit arithmetic, without a branch: below k = 32 the floor quotient,
+// the remainder and half of 2^k all fit, and from k = 32 on the result is 0.)
 __device__ __forceinline__ int32_t round_int(int32_t x, int k)
 {
-    if (k <= 0) return x;
-    if (k > 62) k = 62; // |x| <= 2^31 < g/2
-    const int64_t g = (int64_t)1 << k;
-    int64_t q = (int64_t)x >> k; // floor division
-    const int64_t rem = (int64_t)x - q * g;
-    if (rem > (g >> 1) || (rem == (g >> 1) && (q & 1))) ++q;
-    int64_t r = q * g;
-    if (r > 2147483647ll) r = (2147483647ll >> k) * g;
-    return (int32_t)r;
+    const int s = k < 1 ? 1 : (k > 31 ? 31 : k); // (k < 1: x below)
+    int32_t q = x >> s; // floor division
+    const uint32_t rem = (uint32_t)x & ((1u << s) - 1u), half = 1u << (s - 1);
+    q += rem > half || (rem == half && (q & 1)) ? 1 : 0;
+    uint32_t r = (uint32_t)q << s;
+    if (x >= 0 && r == 0x80000000u) r = 0x7FFFFFFFu & ~((1u << s) - 1u);
+    if (k > 31) r = 0;
+    return k <= 0 ? x : (int32_t)r;
 }
 
 // One integer visibility (re, im); G2 from the exact int64 product of the

@@ -179,3 +179,43 @@ def test_kernels_use_no_scratch(L, tmp_path):
     assert any("k_encode" in n for n, _ in meta) and any("k_decode" in n for n, _ in meta)
     spill = [(n, s) for n, s in meta if s != 0]
     assert not spill, spill
+
+
+def test_no_64bit_shift_by_the_last_register(L, tmp_path):
+    """No kernel shifts a 64-bit value by an amount held in the last vector
+    register of its allocation (granules of 8).  Such shifts have given wrong,
+    varying results on this hardware once many waves ran: the shift by v47 of
+    a kernel with 48 registers, and the compiler does not avoid the form."""
+    import shutil
+    import subprocess
+    from paper_1503_00638_amd import _lib
+    names = [n for n, _ in _gfx950_kernel_metadata(_lib.LIB_PATH, tmp_path)]  # leaves the code objects
+    llvm = "/opt/rocm/llvm/bin"
+    if not os.path.exists(os.path.join(llvm, "llvm-objdump")):
+        pytest.skip("no llvm-objdump")
+    shift = re.compile(r"v_(?:lshlrev_b64|lshrrev_b64|ashrrev_i64)\S* v\[\d+:\d+\], v(\d+),")
+    seen = 0
+    for co in sorted(tmp_path.glob("c*.co")):
+        notes = subprocess.run([os.path.join(llvm, "llvm-readelf"), "--notes", str(co)],
+                               capture_output=True, text=True, check=True).stdout.splitlines()
+        regs = {}
+        name = None
+        for line in notes:
+            if line.strip().startswith(".name:"):
+                name = line.split(":", 1)[1].strip()
+            elif line.strip().startswith(".vgpr_count:"):
+                regs[name] = int(line.split(":", 1)[1])
+        asm = subprocess.run([os.path.join(llvm, "llvm-objdump"), "-d", "--no-show-raw-insn",
+                              "--no-leading-addr", str(co)],
+                             capture_output=True, text=True, check=True).stdout
+        kernel = None
+        for line in asm.splitlines():
+            m = re.match(r"(?:[0-9a-f]+ )?<(\S+)>:", line)
+            if m:
+                kernel = m.group(1)
+                seen += kernel in regs
+            m = shift.search(line)
+            if m and kernel in regs:
+                last = (regs[kernel] + 7) // 8 * 8 - 1
+                assert int(m.group(1)) != last, (kernel, regs[kernel], line.strip())
+    assert seen == len(names)

@@ -44,6 +44,17 @@ def test_round_i32_parity(bsg, F, I, T, seed, f, scale):
     assert np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("F,I,T", [(3, 9, 1), (3, 9, 3), (3, 9, 4), (3, 9, 5), (2, 16, 6), (5, 7, 7),
+                                   (64, 64, 30), (33, 63, 29)])
+def test_round_i32_rows(bsg, F, I, T):
+    """Runs of four visibilities inside one product row, across two and over
+    more, the last ones with a full chip of wavefronts."""
+    vis, autos = synth.gen_vis_int(F, I, T, F + T, N)
+    ref = oracle.round_to_noise_i32(vis, autos, N, 0.01)
+    got = host(bsg.round_to_noise_i32(dev(vis), dev(autos), N, 0.01))
+    assert np.array_equal(got, ref)
+
+
 def test_round_i32_extremes(bsg):
     rng = np.random.default_rng(7)
     F, I, T = 3, 6, 40

@@ -50,6 +50,23 @@ def test_round_parity(bsg, F, I, T, seed, f):
     assert np.array_equal(u32(got), u32(ref))
 
 
+@pytest.mark.parametrize("F,I,T", [(3, 9, 2), (3, 9, 4), (3, 9, 5), (2, 16, 6), (5, 7, 7), (64, 64, 30)])
+def test_round_rows(bsg, F, I, T):
+    """Runs of four visibilities inside one product row, across two and over
+    more; plain, with a product map and with a factor per (frequency, time)."""
+    vis, autos = synth.gen_vis(F, I, T, F + T, N)
+    ref = oracle.round_to_noise(vis, autos, N, 0.01)
+    assert np.array_equal(u32(host(bsg.round_to_noise(dev(vis), dev(autos), N, 0.01))), u32(ref))
+    pm = np.ascontiguousarray(synth.product_pairs(I)[::-1])
+    ref = oracle.round_to_noise(vis, autos, N, 0.01, pm)
+    got = host(bsg.round_to_noise(dev(vis), dev(autos), N, 0.01, prod_map=dev(pm)))
+    assert np.array_equal(u32(got), u32(ref))
+    scale = np.random.default_rng(T).uniform(1e-6, 1.0, (F, T))
+    ref = oracle.round_to_noise_scaled(vis, autos, N, 0.01, scale)
+    got = host(bsg.round_to_noise_scaled(dev(vis), dev(autos), N, 0.01, dev(scale)))
+    assert np.array_equal(u32(got), u32(ref))
+
+
 def test_round_special_values(bsg):
     rng = np.random.default_rng(9)
     F, I, T = 3, 6, 40
