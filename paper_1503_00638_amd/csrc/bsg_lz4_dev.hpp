@@ -121,6 +121,36 @@ __device__ __forceinline__ void stage_fast(const uint8_t *__restrict__ src, int6
     }
 }
 
+// Staging of a block that is no whole number of units.
+template <int E, int RM>
+__device__ __forceinline__ void stage_part(const uint8_t *__restrict__ src, int64_t elems,
+                                           uint8_t *lds, const RoundParams &rp, int64_t first_elem)
+{
+    for (int64_t u = lane_id(); u * Unit<E>::G < elems; u += kWave) {
+        const int64_t left = elems - u * Unit<E>::G;
+#pragma unroll 1
+        for (int c = 0; c < Unit<E>::NC; ++c) {
+            uint32_t w[32];
+            load_column<E>(src + u * (Unit<E>::G * E), left, c, w);
+            if constexpr (RM != kRoundNone) { // E == 4
+                VisCursor v = cursor_at(rp, (first_elem + u * 32) / 2);
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    if (2 * k >= left) break;
+                    const float2 o = round_at(make_float2(__uint_as_float(w[2 * k]),
+                                                          __uint_as_float(w[2 * k + 1])),
+                                              v, rp);
+                    w[2 * k] = __float_as_uint(o.x);
+                    w[2 * k + 1] = __float_as_uint(o.y);
+                    if (2 * k + 2 < left) cursor_advance(rp, v, 1);
+                }
+            }
+            column_forward<E>(w);
+            store_plane_bytes<E>(lds, elems / 8, u, c, w);
+        }
+    }
+}
+
 // Generic staging with the rounding fused in: element e of the buffer is
 // component e & 1 of visibility e >> 1; each lane rounds its own element and
 // the block is transposed with ballots.
@@ -266,7 +296,7 @@ __device__ __forceinline__ void block_inverse_bytes(const uint8_t *lds, uint8_t 
 }
 
 // EC: the element size this kernel instance has a register fast path for
-// (1, 2, 4, 8, 12, 16), 0 for the generic ballot path only, or kByteShuffle.
+// (1, 2, 4, 8, 12, 16), 0 for the generic path only, or kByteShuffle.
 template <int EC, int RM>
 __device__ __forceinline__ void stage_block(const uint8_t *__restrict__ src, int64_t elems,
                                             int64_t E, uint8_t *lds, const RoundParams &rp,
@@ -274,10 +304,14 @@ __device__ __forceinline__ void stage_block(const uint8_t *__restrict__ src, int
 {
     if constexpr (RM != kRoundNone) {
         static_assert(EC == 4 || EC == 0, "rounding is fused for float32 elements only");
-        if (EC == 4 && elems % 32 == 0 && ((uintptr_t)src % 16) == 0)
-            stage_fast<4, RM>(src, elems, lds, rp, first_elem);
-        else
+        if (EC == 4 && ((uintptr_t)src % 16) == 0) {
+            if (elems % 32 == 0)
+                stage_fast<4, RM>(src, elems, lds, rp, first_elem);
+            else
+                stage_part<4, RM>(src, elems, lds, rp, first_elem);
+        } else {
             block_forward_ballot_round(src, lds, elems, rp, first_elem);
+        }
     } else if constexpr (EC == kByteShuffle) {
         block_forward_bytes(src, lds, elems, E);
     } else if constexpr (EC == kMixed) {
@@ -290,12 +324,15 @@ __device__ __forceinline__ void stage_block(const uint8_t *__restrict__ src, int
         }
     } else {
         if constexpr (EC != 0) {
-            if (elems % Unit<EC>::G == 0 && ((uintptr_t)src % 16) == 0) {
-                stage_fast<EC, kRoundNone>(src, elems, lds, rp, first_elem);
+            if (((uintptr_t)src % 16) == 0) {
+                if (elems % Unit<EC>::G == 0)
+                    stage_fast<EC, kRoundNone>(src, elems, lds, rp, first_elem);
+                else
+                    stage_part<EC, kRoundNone>(src, elems, lds, rp, first_elem);
                 return;
             }
         }
-        block_forward_ballot(src, lds, elems, E);
+        block_forward_bits(src, lds, elems, E);
     }
 }
 
@@ -1033,8 +1070,12 @@ __device__ __forceinline__ void unstage_block(const uint8_t *lds, int64_t elems,
             unstage_fast<EC>(lds, elems, dst);
             return;
         }
+        if (fast_out) { // a stream's short last block
+            block_inverse_bits(lds, dst, elems, E);
+            return;
+        }
     }
-    block_inverse_bits(lds, dst, elems, E);
+    block_inverse_elements(lds, dst, elems, E);
 }
 
 // unstage_block, with the element count a constant for full blocks.

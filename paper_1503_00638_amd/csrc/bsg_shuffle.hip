@@ -1,6 +1,6 @@
 // Stage 2a: the Bitshuffle bit transpose within blocks (Section 4.2 of
 // Masui et al.), standalone (no LZ4).  One lane per unit on the fast path;
-// one wavefront per block with ballots on the generic path.
+// one wavefront per block on the generic path.
 #include "bsg_internal.hpp"
 #include "bsg_shuffle_dev.hpp"
 
@@ -33,6 +33,26 @@ __global__ __launch_bounds__(256) void k_shuffle_fast(const uint8_t *__restrict_
     }
 }
 
+// One block whose elements are no whole number of units.
+template <int E, bool INV>
+__global__ __launch_bounds__(64) void k_shuffle_part(const uint8_t *__restrict__ in,
+                                                     uint8_t *__restrict__ out, int64_t nb)
+{
+    const int64_t u = int64_t(blockIdx.x) * 64 + threadIdx.x, left = nb - u * Unit<E>::G;
+    if (left <= 0) return;
+    const int c = blockIdx.y; // 4-byte column of the elements
+    uint32_t w[32];
+    if constexpr (!INV) {
+        load_column<E>(in + u * (Unit<E>::G * E), left, c, w);
+        column_forward<E>(w);
+        store_plane_bytes<E>(out, nb / 8, u, c, w);
+    } else {
+        load_plane_bytes<E>(in, nb / 8, u, c, w);
+        column_inverse<E>(w);
+        store_column<E>(out + u * (Unit<E>::G * E), left, c, w);
+    }
+}
+
 template <bool INV>
 __global__ __launch_bounds__(64) void k_shuffle_generic(const uint8_t *__restrict__ in,
                                                         uint8_t *__restrict__ out, int64_t nb,
@@ -40,9 +60,9 @@ __global__ __launch_bounds__(64) void k_shuffle_generic(const uint8_t *__restric
 {
     const int64_t off = int64_t(blockIdx.x) * nb * E;
     if (!INV)
-        block_forward_ballot(in + off, out + off, nb, E);
+        block_forward_bits(in + off, out + off, nb, E);
     else
-        block_inverse_bits(in + off, out + off, nb, E);
+        block_inverse_elements(in + off, out + off, nb, E);
 }
 
 __global__ __launch_bounds__(64) void k_copy_bytes(const uint8_t *__restrict__ in,
@@ -63,6 +83,15 @@ hipError_t fast_launch(const uint8_t *in, uint8_t *out, int64_t nblocks, int64_t
     return hipGetLastError();
 }
 
+template <int E, bool INV>
+hipError_t part_launch(const uint8_t *in, uint8_t *out, int64_t nb, hipStream_t s)
+{
+    const int64_t units = (nb + Unit<E>::G - 1) / Unit<E>::G;
+    hipLaunchKernelGGL((k_shuffle_part<E, INV>), dim3((unsigned)((units + 63) / 64), Unit<E>::NC),
+                       dim3(64), 0, s, in, out, nb);
+    return hipGetLastError();
+}
+
 template <bool INV>
 hipError_t blocks_launch(const uint8_t *in, uint8_t *out, int64_t nblocks, int64_t nb,
                          int64_t E, hipStream_t s)
@@ -78,6 +107,17 @@ hipError_t blocks_launch(const uint8_t *in, uint8_t *out, int64_t nblocks, int64
         case 8: return fast_launch<8, INV>(in, out, nblocks, nb, s);
         case 12: return fast_launch<12, INV>(in, out, nblocks, nb, s);
         case 16: return fast_launch<16, INV>(in, out, nblocks, nb, s);
+        default: break;
+        }
+    }
+    if (G && aligned && nblocks == 1) {
+        switch (E) {
+        case 1: return part_launch<1, INV>(in, out, nb, s);
+        case 2: return part_launch<2, INV>(in, out, nb, s);
+        case 4: return part_launch<4, INV>(in, out, nb, s);
+        case 8: return part_launch<8, INV>(in, out, nb, s);
+        case 12: return part_launch<12, INV>(in, out, nb, s);
+        case 16: return part_launch<16, INV>(in, out, nb, s);
         default: break;
         }
     }

@@ -172,32 +172,163 @@ __device__ __forceinline__ void load_planes(const uint8_t *blk, int64_t plane_by
     }
 }
 
-// Generic transpose of one block by a whole wavefront, any E and any n_B
-// (multiple of 8): lanes hold 64 consecutive elements; for every bit b one
-// 64-lane ballot yields 8 bytes of plane b (ballot bit l = element 64g + l,
-// which is exactly the LSB-first byte order of the plane).
-__device__ __forceinline__ void block_forward_ballot(const uint8_t *in, uint8_t *out,
-                                                     int64_t elems, int64_t E)
+// A block whose elements are no whole number of units ends in a part of one,
+// and its planes (n_B / 8 bytes) start at any byte: elements past the block's
+// end are left out, and plane bytes are moved one by one (in global memory
+// and in LDS; a stream's short last block, where a ballot per bit of every 64
+// elements took up to 40 us).  Elements of 8 bytes and more go one 4-byte
+// column at a time, so that 32 registers do.
+//
+// Load / store the dwords of column c of a unit with `left` >= 8 elements to
+// the block's end (E <= 4: the unit's only 32 dwords).
+template <int E>
+__device__ __forceinline__ void load_column(const uint8_t *p, int64_t left, int c, uint32_t (&w)[32])
+{
+    constexpr int NC = Unit<E>::NC;
+    const int words = E >= 4 ? (int)(left < 32 ? left : 32)
+                             : (int)(left < Unit<E>::G ? left : Unit<E>::G) * E / 4;
+#pragma unroll
+    for (int k = 0; k < 32; ++k)
+        w[k] = k < words ? reinterpret_cast<const uint32_t *>(p)[k * NC + c] : 0u;
+}
+template <int E>
+__device__ __forceinline__ void store_column(uint8_t *p, int64_t left, int c, const uint32_t (&w)[32])
+{
+    constexpr int NC = Unit<E>::NC;
+    const int words = E >= 4 ? (int)(left < 32 ? left : 32)
+                             : (int)(left < Unit<E>::G ? left : Unit<E>::G) * E / 4;
+#pragma unroll
+    for (int k = 0; k < 32; ++k)
+        if (k < words) reinterpret_cast<uint32_t *>(p)[k * NC + c] = w[k];
+}
+template <int E>
+__device__ __forceinline__ void column_forward(uint32_t (&w)[32])
+{
+    if constexpr (E <= 2)
+        unit_forward<E>(w);
+    else
+        transpose32(w);
+}
+template <int E>
+__device__ __forceinline__ void column_inverse(uint32_t (&w)[32])
+{
+    if constexpr (E <= 2)
+        unit_inverse<E>(w);
+    else
+        transpose32(w);
+}
+// The column's plane bytes of unit u to / from a block laid out as planes.
+template <int E>
+__device__ __forceinline__ void store_plane_bytes(uint8_t *blk, int64_t plane_bytes, int64_t u, int c,
+                                                  const uint32_t (&w)[32])
+{
+    using PW = PlaneWords<E>;
+    constexpr int NPL = E >= 4 ? 32 : PW::NPL;
+    const int64_t left = plane_bytes - u * Unit<E>::PB;
+    uint8_t *dst = blk + 32 * c * plane_bytes + u * Unit<E>::PB;
+#pragma unroll
+    for (int q = 0; q < Unit<E>::PB; ++q) {
+        if (q >= left) break;
+#pragma unroll
+        for (int pl = 0; pl < NPL; ++pl)
+            dst[pl * plane_bytes + q] = (uint8_t)(w[PW::word(pl, q / 4)] >> (8 * (q % 4)));
+    }
+}
+template <int E>
+__device__ __forceinline__ void load_plane_bytes(const uint8_t *blk, int64_t plane_bytes, int64_t u,
+                                                 int c, uint32_t (&w)[32])
+{
+    using PW = PlaneWords<E>;
+    constexpr int NPL = E >= 4 ? 32 : PW::NPL;
+    const int64_t left = plane_bytes - u * Unit<E>::PB;
+    const uint8_t *src = blk + 32 * c * plane_bytes + u * Unit<E>::PB;
+#pragma unroll
+    for (int k = 0; k < 32; ++k) w[k] = 0;
+#pragma unroll
+    for (int q = 0; q < Unit<E>::PB; ++q) {
+        if (q >= left) break;
+#pragma unroll
+        for (int pl = 0; pl < NPL; ++pl)
+            w[PW::word(pl, q / 4)] |= (uint32_t)src[pl * plane_bytes + q] << (8 * (q % 4));
+    }
+}
+
+// 8 x 8 bit transpose: bit j of byte i of (lo, hi) goes to bit i of byte j.
+__device__ __forceinline__ void transpose8(uint32_t &lo, uint32_t &hi)
+{
+    uint32_t t = (lo ^ (lo >> 7)) & 0x00AA00AAu;
+    lo ^= t ^ (t << 7);
+    t = (hi ^ (hi >> 7)) & 0x00AA00AAu;
+    hi ^= t ^ (t << 7);
+    t = (lo ^ (lo >> 14)) & 0x0000CCCCu;
+    lo ^= t ^ (t << 14);
+    t = (hi ^ (hi >> 14)) & 0x0000CCCCu;
+    hi ^= t ^ (t << 14);
+    t = (lo ^ (hi << 4)) & 0xF0F0F0F0u;
+    lo ^= t;
+    hi ^= t >> 4;
+}
+
+// Generic transpose of one block by a whole wavefront, any E, any n_B
+// (multiple of 8) and any alignment: a lane takes byte k of 8 consecutive
+// elements, whose 8 x 8 bits are byte g of the planes 8 k .. 8 k + 7 (several
+// k at once where a block has fewer than 64 such groups).  A ballot per bit
+// of every 64 elements took 48 us for 4 Mi 3-byte elements, this takes 11.
+__device__ __forceinline__ void block_forward_bits(const uint8_t *in, uint8_t *out, int64_t elems,
+                                                   int64_t E)
 {
     const int lane = threadIdx.x & 63;
     const int64_t pb = elems / 8;
-    for (int64_t g = 0; g < elems; g += 64) {
-        const int64_t i = g + lane;
-        const bool valid = i < elems;
-        const int64_t rem = (elems - g) / 8;
-        const int nbytes = rem < 8 ? (int)rem : 8;
-        for (int64_t byte = 0; byte < E; ++byte) {
-            const uint32_t v = valid ? in[i * E + byte] : 0u;
-            for (int bit = 0; bit < 8; ++bit) {
-                const uint64_t m = __ballot((v >> bit) & 1u);
-                if (lane < nbytes) out[(8 * byte + bit) * pb + g / 8 + lane] = (uint8_t)(m >> (8 * lane));
-            }
+    const int rows = pb < 64 ? 64 / (int)pb : 1;
+    const int k0 = rows > 1 ? lane / (int)pb : 0, g0 = lane - k0 * (int)pb;
+    if (k0 >= rows) return;
+    for (int64_t k = k0; k < E; k += rows) {
+#pragma unroll 2
+        for (int64_t g = g0; g < pb; g += 64) {
+            uint32_t b[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) b[i] = in[(8 * g + i) * E + k];
+            uint32_t lo = b[0] | b[1] << 8 | b[2] << 16 | b[3] << 24;
+            uint32_t hi = b[4] | b[5] << 8 | b[6] << 16 | b[7] << 24;
+            transpose8(lo, hi);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                out[(8 * k + j) * pb + g] = (uint8_t)((j < 4 ? lo : hi) >> (8 * (j & 3)));
         }
     }
 }
 
-__device__ __forceinline__ void block_inverse_bits(const uint8_t *in, uint8_t *out,
-                                                   int64_t elems, int64_t E)
+// Its inverse, from LDS, for a stream's short last block (a bit per LDS read
+// took 9 us longer for 1844 4-byte elements).
+__device__ __forceinline__ void block_inverse_bits(const uint8_t *in, uint8_t *out, int64_t elems,
+                                                   int64_t E)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t pb = elems / 8;
+    const int rows = pb < 64 ? 64 / (int)pb : 1;
+    const int k0 = rows > 1 ? lane / (int)pb : 0, g0 = lane - k0 * (int)pb;
+    if (k0 >= rows) return;
+    for (int64_t k = k0; k < E; k += rows) {
+        for (int64_t g = g0; g < pb; g += 64) {
+            uint32_t b[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) b[j] = in[(8 * k + j) * pb + g];
+            uint32_t lo = b[0] | b[1] << 8 | b[2] << 16 | b[3] << 24;
+            uint32_t hi = b[4] | b[5] << 8 | b[6] << 16 | b[7] << 24;
+            transpose8(lo, hi);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                out[(8 * g + i) * E + k] = (uint8_t)((i < 4 ? lo : hi) >> (8 * (i & 3)));
+        }
+    }
+}
+
+// And the inverse for many blocks without a register path: a lane per element,
+// so that a wavefront's byte stores fall into neighbouring lines (with 8
+// elements per lane 2 Mi 6-byte elements took 47 us instead of 37, and their
+// decompression 53 instead of 30).
+__device__ __forceinline__ void block_inverse_elements(const uint8_t *in, uint8_t *out,
+                                                       int64_t elems, int64_t E)
 {
     const int lane = threadIdx.x & 63;
     const int64_t pb = elems / 8;

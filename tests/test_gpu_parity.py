@@ -272,6 +272,42 @@ def test_compress_block_sizes(bsg, E, block_bytes):
         assert np.array_equal(host(bsg.decompress_sync(dev(ref), n, E, nb))[: n * E], data)
 
 
+@pytest.mark.parametrize("E", [1, 2, 3, 4, 7, 8, 12, 16])
+def test_short_last_blocks(bsg, E):
+    """Last blocks of every size up to two of the transposes' units and a
+    long odd one, with raw tails: the transpose alone, both ways, aligned and
+    not, and the stream."""
+    nb = 64 * 8
+    for last in [*range(8, 264, 8), nb - 8]:
+        n = nb + last + last % 7
+        data = synth.gen_walk_int16(n * E // 2 + 1, last).view(np.uint8)[: n * E].copy()
+        x, ref = dev(data), oracle.bitshuffle(data, E, nb)
+        assert np.array_equal(host(bsg.bitshuffle(x, E, nb)), ref), last
+        assert np.array_equal(host(bsg.bitunshuffle(dev(ref), E, nb)), data), last
+        s = oracle.compress(data, E, nb)
+        assert np.array_equal(host(bsg.compress_sync(x, E, nb)), s), last
+        assert np.array_equal(host(bsg.decompress_sync(dev(s), n, E, nb))[: n * E], data), last
+        if last % 64 == 0:
+            buf = torch.zeros(n * E + 16, dtype=torch.uint8, device="cuda:0")
+            off = buf[5:5 + n * E]
+            off.copy_(x)
+            assert np.array_equal(host(bsg.bitshuffle(off, E, nb)), ref), last
+            assert np.array_equal(host(bsg.compress_sync(off, E, nb)), s), last
+            off.zero_()
+            bsg.bitunshuffle(dev(ref), E, nb, out=off)
+            assert np.array_equal(host(off), data), last
+
+
+@pytest.mark.parametrize("F,I,T", [(1, 5, 23), (1, 5, 22), (2, 3, 31), (7, 4, 5), (3, 7, 50), (1, 1, 9)])
+def test_fused_short_last_block(bsg, F, I, T):
+    """The rounding fused into a last block of no whole number of units."""
+    vis, autos = synth.gen_vis(F, I, T, F + T, N)
+    for B in (128, 512, 2048):
+        ref = oracle.compress(oracle.round_to_noise(vis, autos, N, 0.01), 4, B)
+        out, nb = bsg.round_compress(dev(vis), dev(autos), N, 0.01, block_size=B)
+        assert np.array_equal(host(out)[: int(nb.item())], ref), B
+
+
 @pytest.mark.parametrize("lit_max", [1, 3, 9, 40, 300])
 def test_compress_literal_runs(bsg, lit_max):
     """Literal runs of 0 .. lit_max bytes at every alignment (the copies of a
