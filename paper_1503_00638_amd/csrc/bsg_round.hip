@@ -322,11 +322,12 @@ hipError_t launch_noise_comp(const float *vis, const RoundParams &rp, double *sc
     const int64_t fit = lds ? kCompAutos / std::max<int64_t>(rp.I, 1) : kCompThreads;
     const int Tb = (int)std::min<int64_t>({rp.T, kCompThreads, fit});
     const int64_t tiles = (rp.T + Tb - 1) / Tb;
+    const int64_t most = lds ? kCompPairs : 1 << 28; // products of a workgroup
     // Enough parts for three workgroups per CU (as many as reside), if each
     // keeps four steps, and for the table.
     const int64_t steps = rp.P / (kCompAhead * (kCompThreads / Tb));
     const int parts = (int)std::max<int64_t>(
-        {(rp.P + kCompPairs - 1) / kCompPairs, 1,
+        {(rp.P + most - 1) / most, 1,
          std::min<int64_t>(steps / 4, (3 * 256 + rp.F * tiles - 1) / (rp.F * tiles))});
     if (parts > 1) {
         hipLaunchKernelGGL(k_ones, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256),

@@ -76,7 +76,7 @@ def test_compensation_degenerate_inputs(bsg, T):
 
 
 @pytest.mark.parametrize("F,I,T", [(1, 128, 32), (2, 40, 1), (3, 12, 513), (1, 9, 1100), (2, 61, 50),
-                                   (1, 200, 7), (600, 3, 5)])
+                                   (1, 200, 7), (600, 3, 5), (1, 512, 32)])
 def test_compensation_shapes_and_scales(bsg, F, I, T):
     """Products over several workgroups, times of every kind, and a float32
     screening that has to let every product through that matters: autos and
