@@ -6,10 +6,13 @@
 // pass (payload, offsets, header, capacity verdict, raw tail).  One class
 // holds chunks of all common element sizes: a launch per element size ran
 // one after the other, 220 us instead of 89 to compress 16 chunks of up to
-// 1 MiB and 112 instead of 41 to decompress them.  Nothing is allocated and nothing is synchronised with the
-// host, so the whole sequence can be captured into a hipGraph.
+// 1 MiB and 112 instead of 41 to decompress them.  Only an element size with
+// many blocks has a class and a decoder of its own (kOwnMinBlocks).  Nothing
+// is allocated and nothing is synchronised with the host, so the whole
+// sequence can be captured into a hipGraph.
 #include <algorithm>
 #include <cstring>
+#include <map>
 #include <numeric>
 #include <vector>
 
@@ -26,7 +29,16 @@ constexpr int64_t kBatchSideMinBlocks = 16384;
 // that its scan and pack run beside the next one's encode.
 constexpr int kMaxParts = 8;
 constexpr int64_t kPartMinBlocks = 8192;
-static_assert(kMaxClasses >= 3 * 4 + kMaxParts, "classes of a batch");
+// An element size of 1, 2, 4 or 8 bytes with at least this many blocks of one
+// instance block size is a class of its own, which its own decoder takes: the
+// mixed decoder's registers leave 16 workgroups per CU where the others have
+// 18.  Below, the end of one more launch costs more than that gives.
+// 37 GiB in 4096 chunks of 2, 4 and 8 bytes (1.5 M blocks and more each):
+// decompress 33.6 ms, 34.7 as one mixed class.  0.78 GB in 256 chunks (about
+// 32,000 blocks each): 659 us mixed, 707 in classes of their own.
+constexpr int64_t kOwnMinBlocks = 65536;
+constexpr int kKeysPerSize = 7; // mixed, 1, 2, 4, 8, 12, 16
+static_assert(kMaxClasses >= kKeysPerSize * 4 + kMaxParts, "classes of a batch");
 
 struct BatchHeader {
     int32_t count, n_classes;
@@ -34,7 +46,7 @@ struct BatchHeader {
 };
 
 // Consecutive chunks (in table order) whose blocks one launch takes: same
-// element class (12, 16, or kMixed for the others) and instance block size.
+// element class (kKeyClass) and instance block size.
 struct BatchClass {
     int32_t ec, maxb, first_chunk, n_chunks;
     int64_t first_block, n_blocks;
@@ -50,6 +62,16 @@ struct BatchChunk {
     int64_t slot_bytes;
     int32_t E, orig;     // element size, index in the caller's array
 };
+
+// Element class of a key; place of an element class in it.
+constexpr int kKeyClass[kKeysPerSize] = {kMixed, 1, 2, 4, 8, 12, 16};
+
+int key_of(int ec)
+{
+    for (int i = 1; i < kKeysPerSize; ++i)
+        if (kKeyClass[i] == ec) return i;
+    return 0;
+}
 
 constexpr int64_t table_bytes(int64_t count)
 {
@@ -148,8 +170,16 @@ __global__ __launch_bounds__(64) void k_batch_encode(const uint8_t *__restrict__
     }
 }
 
+// As dec_waves_per_eu, but 4 for 4 KiB blocks of 8-byte elements, whose
+// registers beside the block walk's do not fit 5 without spills.
+template <int MAXB, int EC> constexpr int bdec_waves_per_eu()
+{
+    constexpr int n = dec_waves_per_eu<MAXB, EC>();
+    return EC == 8 && n > 4 ? 4 : n;
+}
+
 template <int MAXB, int EC>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(dec_waves_per_eu<MAXB, EC>()))) void k_batch_decode(const uint8_t *__restrict__ table, BatchClass C,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(bdec_waves_per_eu<MAXB, EC>()))) void k_batch_decode(const uint8_t *__restrict__ table, BatchClass C,
                                                      int32_t *__restrict__ status, int schedule)
 {
     __shared__ DecLds<MAXB> L;
@@ -357,6 +387,10 @@ hipError_t bdec_dispatch(const uint8_t *t, const BatchClass &C, int wpc, int sch
 {
     return for_block_size(C.maxb, [&](auto maxb) {
         switch (C.ec) {
+        case 1: return launch_bdec<maxb.value, 1>(t, C, wpc, sched, status, s);
+        case 2: return launch_bdec<maxb.value, 2>(t, C, wpc, sched, status, s);
+        case 4: return launch_bdec<maxb.value, 4>(t, C, wpc, sched, status, s);
+        case 8: return launch_bdec<maxb.value, 8>(t, C, wpc, sched, status, s);
         case 12: return launch_bdec<maxb.value, 12>(t, C, wpc, sched, status, s);
         case 16: return launch_bdec<maxb.value, 16>(t, C, wpc, sched, status, s);
         default: return launch_bdec<maxb.value, kMixed>(t, C, wpc, sched, status, s);
@@ -404,6 +438,7 @@ int bsg_batch_build_table(const bsg_chunk *chunks, int32_t count, void *host_tab
         return BSG_EINVAL;
     std::vector<BatchChunk> rows(count);
     std::vector<int> key(count);
+    std::map<int, int64_t> blocks; // by key
     for (int i = 0; i < count; ++i) {
         const bsg_chunk &c = chunks[i];
         Layout L;
@@ -425,10 +460,12 @@ int bsg_batch_build_table(const bsg_chunk *chunks, int32_t count, void *host_tab
         r.E = (int32_t)c.elem_size;
         r.orig = i;
         // class key: the instance's block size and element class
-        const int ec = element_class(c.elem_size);
-        key[i] = for_block_size(L.block_bytes(), [](auto m) { return m.value; }) * 4 +
-                 (ec == 12 ? 1 : ec == 16 ? 2 : 0);
+        key[i] = for_block_size(L.block_bytes(), [](auto m) { return m.value; }) * kKeysPerSize +
+                 key_of(element_class(c.elem_size));
+        blocks[key[i]] += r.n_blocks;
     }
+    for (int &k : key) // common element sizes with few blocks share a class
+        if (kKeyClass[k % kKeysPerSize] <= 8 && blocks[k] < kOwnMinBlocks) k -= k % kKeysPerSize;
     std::vector<int> order(count);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key[a] < key[b]; });
@@ -447,9 +484,9 @@ int bsg_batch_build_table(const bsg_chunk *chunks, int32_t count, void *host_tab
         BatchChunk r = rows[order[k]];
         const int kk = key[order[k]];
         if (k == 0 || kk != key[order[k - 1]] || cls[nc - 1].n_blocks >= part) {
-            BatchClass &C = cls[nc++]; // at most 3 x 4 keys and kMaxParts more
-            C.ec = kk % 4 == 1 ? 12 : kk % 4 == 2 ? 16 : kMixed;
-            C.maxb = kk / 4;
+            BatchClass &C = cls[nc++]; // at most 7 x 4 keys and kMaxParts more
+            C.ec = kKeyClass[kk % kKeysPerSize];
+            C.maxb = kk / kKeysPerSize;
             C.first_chunk = k;
             C.first_block = blk;
         }

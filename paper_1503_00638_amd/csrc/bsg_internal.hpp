@@ -193,7 +193,7 @@ int64_t compress_workspace(const Layout &L);
 // events) and makes both streams wait for the caller's work so far;
 // side_streams_end makes the caller's stream wait for the pack stream and
 // for event done[last_enc] of the encode stream.
-constexpr int kSideEvents = 24;
+constexpr int kSideEvents = 36;
 struct SideStreams {
     bool made = false, ok = false;
     hipStream_t enc = nullptr, pack = nullptr;

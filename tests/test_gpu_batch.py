@@ -115,6 +115,29 @@ def test_batch_split_classes(bsg, blocks):
         assert np.array_equal(host(dplan.outs[k])[: d.size], d), k
 
 
+@pytest.mark.parametrize("E", [1, 2, 4, 8])
+@pytest.mark.parametrize("extra", [-1, 0])
+def test_batch_own_class(bsg, E, extra):
+    """An element size with 65,536 blocks (one short of it for extra -1) in
+    one instance block size, beside chunks of the other element sizes."""
+    B = max(32 // E // 8 * 8, 8)  # elements per block
+    specs = [(E, B, B * (65536 + extra - 100)), (2, 512, 5000), (4, 256, 2567), (E, B, B * 100),
+             (3, 8, 8 * 99 + 5), (8, 128, 1280), (1, 1024, 1024 * 9), (12, 8, 300)]
+    specs[1:] = [(e, b, n) for e, b, n in specs[1:] if e != E or b == B]
+    data = [chunk_data(k, e, n) for k, (e, _, n) in enumerate(specs)]
+    Es, Bs = [e for e, _, _ in specs], [b for _, b, _ in specs]
+    refs = [oracle.compress(d, e, b) for d, e, b in zip(data, Es, Bs)]
+    plan = bsg.BatchPlan.for_compress([to_dev(d) for d in data], Es, Bs)
+    nb = host(plan.compress())
+    for k, ref in enumerate(refs):
+        assert nb[k] == ref.size and np.array_equal(host(plan.outs[k])[: ref.size], ref), k
+    streams = [dev(r) for r in refs]
+    dplan = bsg.BatchPlan.for_decompress(streams, [r.size for r in refs], [n for _, _, n in specs], Es, Bs)
+    assert not host(dplan.decompress()).any()
+    for k, d in enumerate(data):
+        assert np.array_equal(host(dplan.outs[k])[: d.size], d), k
+
+
 def test_batch_launch_shape_does_not_change_bytes(bsg):
     data, Es, Bs = mixed()
     xs = [to_dev(d) for d in data]
