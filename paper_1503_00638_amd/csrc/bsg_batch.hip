@@ -30,9 +30,11 @@ constexpr int64_t kBatchSideMinBlocks = 16384;
 constexpr int kMaxParts = 8;
 constexpr int64_t kPartMinBlocks = 8192;
 // An element size of 1, 2, 4 or 8 bytes with at least this many blocks of one
-// instance block size is a class of its own, which its own decoder takes: the
-// mixed decoder's registers leave 16 workgroups per CU where the others have
-// 18.  Below, the end of one more launch costs more than that gives.
+// instance block size is a class of its own, which its own decoder takes: in
+// 8 KiB blocks the mixed decoder's 128 registers leave 16 workgroups per CU,
+// where those for 1, 2 and 4 bytes (95) have the 18 that LDS allows and the
+// one for 8 takes 109.  Below, the end of one more launch costs more than
+// that gives.
 // 37 GiB in 4096 chunks of 2, 4 and 8 bytes (1.5 M blocks and more each):
 // decompress 33.6 ms, 34.7 as one mixed class.  0.78 GB in 256 chunks (about
 // 32,000 blocks each): 659 us mixed, 707 in classes of their own.
