@@ -404,7 +404,7 @@ def bench_batch(args, torch, bsg):
     comp, dcm = float(np.median(comp_ms)), float(np.median(dec_ms))
     gbps = lambda ms: round(U / (ms * 1e-3) / 1e9, 2)
     enc_bytes, dec_bytes = U + C, C + U
-    dominant = ("k_batch_encode+scan+finish+pack (batch compress)", comp, enc_bytes) \
+    dominant = ("k_batch_encode+scan+k_batch_pack (batch compress)", comp, enc_bytes) \
         if comp >= dcm else ("k_batch_decode+k_batch_dec_tail (batch decompress)", dcm, dec_bytes)
     achieved = dominant[2] / (dominant[1] * 1e-3) / 1e9
     res = {
