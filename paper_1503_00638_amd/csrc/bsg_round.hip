@@ -157,11 +157,14 @@ __global__ __launch_bounds__(256) void k_round(const V2 *__restrict__ vin, V2 *_
 // 30 times: 20.8 ms -> 30 us).  So a product is first screened
 // in float32 against the lowest term any thread has found for its time
 // (`best`): with q = |V_ij|^2, ab = V_ii V_jj and c = ab (1 - best)(1 -
-// 2^-18), all rounded to float32, q <= c with c finite and at least 1e-30
-// (where underflow in q is far below the margin) puts the exact quotient
-// below (1 - best)(1 - 2^-20), so the exact term, rounded, is not below
-// best.  Where that fails (products that lower the minimum, or without
-// a usable ab) the exact path follows, which is soon rare.
+// 2^-18), all rounded to float32, a product with q <= c is left out where
+// every factor of the comparison is good to a few parts in 2^24: ab a normal
+// float (a subnormal one is off by up to a half), c at least 1e-30 (where
+// underflow in q is far below the margin) and finite.  That puts the exact
+// quotient below (1 - best)(1 - 2^-20), so the exact term, rounded, is not
+// below best, and the minimum is the one of all exact terms.  Where any of it
+// fails (products that lower the minimum, or without a usable ab) the exact
+// path follows, which is soon rare.
 constexpr int kCompThreads = 512;
 constexpr int kCompAhead = 8;       // visibilities a thread loads before it uses the first
 constexpr int kCompPairs = 8192;    // products a workgroup has a table for (32 KiB)
@@ -245,7 +248,7 @@ __global__ __launch_bounds__(kCompThreads) void k_noise_comp(const float2 *__res
                     const bool cross = autos_of(p + u * R + r, ai[u], aj[u]);
                     const float q = v[u].x * v[u].x + v[u].y * v[u].y, ab = ai[u] * aj[u];
                     const float c = thr * ab;
-                    need[u] = cross && !(q <= c && c >= 1e-30f && c < __builtin_inff());
+                    need[u] = cross && !(q <= c && c >= 1e-30f && c < __builtin_inff() && ab >= 0x1p-126f);
                     any |= need[u];
                 }
                 if (any) {

@@ -116,3 +116,39 @@ def test_compensation_prod_map(bsg):
     ref = oracle.noise_compensation(vis, autos, prod_map=pm)
     got = host(bsg.noise_compensation(dev(vis), dev(autos), prod_map=dev(pm)))
     assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
+
+
+@pytest.mark.parametrize("I,T", [(64, 32), (128, 7), (256, 32)])
+@pytest.mark.parametrize("ab,ratio", [(1e-45, 1e15), (3e-42, 1e12), (1e-39, 1e9), (1e-38, 1e9)])
+def test_compensation_subnormal_auto_products(bsg, I, T, ab, ratio):
+    """V_ii V_jj below the normal float32 range under cross products far above
+    it: the float32 product is off by up to a half there, so it must not decide
+    which terms can be the minimum.  Every time has its first products near the
+    lowest term and hundreds of later ones just above and below it."""
+    rng = np.random.default_rng(I + T)
+    P = I * (I + 1) // 2
+    autos = (np.sqrt(ab) * 10.0 ** rng.uniform(-0.5, 0.5, (2, I, T))).astype(np.float32)
+    pairs = synth.product_pairs(I)
+    prod = autos[:, pairs[:, 0]].astype(np.float64) * autos[:, pairs[:, 1]].astype(np.float64)
+    r = ratio * rng.uniform(1.0, 1.3, (2, P, T))
+    vis = np.sqrt(r * prod).astype(np.complex64)
+    ref = oracle.noise_compensation(vis, autos)
+    assert (ref < -0.9 * ratio).all()
+    got = host(bsg.noise_compensation(dev(vis), dev(autos)))
+    assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
+
+
+@pytest.mark.parametrize("lo,hi", [(-45, 38), (-24, -18), (-20, 19)])
+def test_compensation_over_the_float32_range(bsg, lo, hi):
+    """Autos and visibilities each anywhere in the float32 range (subnormal
+    ones too), independent of each other."""
+    rng = np.random.default_rng(hi - lo)
+    F, I, T = 3, 96, 32
+    P = I * (I + 1) // 2
+    with np.errstate(over="ignore", under="ignore"):
+        autos = (10.0 ** rng.uniform(lo, hi, (F, I, T))).astype(np.float32)
+        vis = (10.0 ** rng.uniform(lo, hi, (F, P, T, 2))).astype(np.float32)
+    vis = vis.view(np.complex64)[..., 0]
+    ref = oracle.noise_compensation(vis, autos)
+    got = host(bsg.noise_compensation(dev(vis), dev(autos)))
+    assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
