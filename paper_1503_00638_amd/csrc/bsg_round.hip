@@ -139,12 +139,14 @@ __global__ __launch_bounds__(256) void k_round(const V2 *__restrict__ vin, V2 *_
 // Compensation of the diagonal noise model (Section 3.2): per (frequency,
 // time) the minimum over cross products of 1 - |V_ij|^2 / (V_ii V_jj), in
 // double and in that order (products with V_ii V_jj not positive and finite
-// skipped, 1 when none is left).  A workgroup of 512 threads takes Tb <= 512
-// times and up to kCompPairs products, of one frequency after the other:
-// thread k takes time k mod Tb and every R-th product from k / Tb (R = 512 /
-// Tb), so each step of the workgroup reads about 4 KiB of the contiguous
-// [P][T] block.  The places of a product's two autos come from a table in LDS
-// made once, the frequency's autos are in LDS too.  The per-thread minima
+// skipped, 1 when none is left).  A workgroup of 512 threads (1024 where the
+// grid leaves CUs empty: 24 inputs, 64 times 13.2 -> 10.3 us) takes Tb times
+// and up to kCompPairs products, of one frequency after the other: thread k
+// takes time k mod Tb and every R-th product from k / Tb (R = threads / Tb), so
+// each step of the workgroup reads R runs of 8 Tb bytes (one contiguous piece
+// of the [P][T] block where Tb = T).  The places of a product's two autos come
+// from a table in LDS made once, the frequency's autos are in LDS too: above
+// 128 inputs they bound Tb (8 at 2048 inputs: 32 times in 279 us, 1.9 TB/s).  The per-thread minima
 // meet in LDS, those of several workgroups in an atomic minimum on the
 // output, set to 1 before.  The minimum does not depend on the order of the
 // terms (no term is -0, NaN terms are skipped).
@@ -166,6 +168,8 @@ __global__ __launch_bounds__(256) void k_round(const V2 *__restrict__ vin, V2 *_
 // fails (products that lower the minimum, or without a usable ab) the exact
 // path follows, which is soon rare.
 constexpr int kCompThreads = 512;
+constexpr int kCompTimes = 128;     // times of a workgroup (105 MB of 11 inputs, 512 times:
+                                    // 31 us at 64, 27 at 128, 29 at 256, 35 at 512)
 constexpr int kCompAhead = 8;       // visibilities a thread loads before it uses the first
 constexpr int kCompPairs = 8192;    // products a workgroup has a table for (32 KiB)
 constexpr int kCompAutos = 16384;   // autos of one frequency and Tb times (64 KiB)
@@ -173,17 +177,16 @@ constexpr int kCompAutos = 16384;   // autos of one frequency and Tb times (64 K
 // LDS: i Tb and j Tb of the workgroup's products fit 16 bits each and the
 // autos their place; else (more inputs than kCompAutos) both are found again
 // for each product.
-template <bool LDS>
-__global__ __launch_bounds__(kCompThreads) void k_noise_comp(const float2 *__restrict__ vis,
-                                                             RoundParams rp,
-                                                             double *__restrict__ scale, int Tb,
-                                                             int parts)
+template <bool LDS, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_noise_comp(const float2 *__restrict__ vis,
+                                                        RoundParams rp, double *__restrict__ scale,
+                                                        int Tb, int parts)
 {
-    __shared__ double part[kCompThreads];
-    __shared__ double best[kCompThreads]; // per time; many threads write it, any term found will do
+    __shared__ double part[THREADS];
+    __shared__ double best[THREADS]; // per time; many threads write it, any term found will do
     extern __shared__ uint32_t dyn[];     // LDS: the products' table, then the autos
     const int k = threadIdx.x;
-    const int R = kCompThreads / Tb, r = k / Tb, tl = k - r * Tb;
+    const int R = THREADS / Tb, r = k / Tb, tl = k - r * Tb;
     const int64_t T = rp.T, t0 = (int64_t)blockIdx.z * Tb, t = t0 + tl;
     const int64_t per = (rp.P + parts - 1) / parts, first = per * blockIdx.y;
     const int count = (int)(rp.P - first < per ? (rp.P > first ? rp.P - first : 0) : per);
@@ -191,7 +194,7 @@ __global__ __launch_bounds__(kCompThreads) void k_noise_comp(const float2 *__res
     float *la = reinterpret_cast<float *>(dyn + per);
     const bool mine = r < R && t < T;
     if constexpr (LDS) {
-        for (int p = k; p < count; p += kCompThreads) {
+        for (int p = k; p < count; p += THREADS) {
             int32_t i, j;
             product_pair(rp, first + p, i, j);
             pairs[p] = (uint32_t)(i * Tb) | (uint32_t)(j * Tb) << 16;
@@ -201,7 +204,7 @@ __global__ __launch_bounds__(kCompThreads) void k_noise_comp(const float2 *__res
         const float2 *vbase = vis + (fr * rp.P + first) * T;
         const float *abase = rp.autos + fr * rp.I * T;
         if constexpr (LDS) {
-            for (int e = k; e < (int)rp.I * Tb; e += kCompThreads) {
+            for (int e = k; e < (int)rp.I * Tb; e += THREADS) {
                 const int i = e / Tb;
                 const int64_t ta = t0 + e - i * Tb;
                 la[e] = ta < T ? abase[i * T + ta] : 0.0f;
@@ -283,6 +286,41 @@ __global__ __launch_bounds__(kCompThreads) void k_noise_comp(const float2 *__res
     }
 }
 
+// Small arrays: a thread takes one (frequency, time) and walks its products.
+// A workgroup of the kernel above spends five barriers on each frequency,
+// which 1 to 36 products do not fill: 1,000,000 frequencies of 2 inputs and 7
+// times took 2750 us there, 30 here (HBM).
+__global__ __launch_bounds__(256) void k_noise_comp_small(const float2 *__restrict__ vis,
+                                                          RoundParams rp,
+                                                          double *__restrict__ scale, int64_t n)
+{
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
+        int64_t fr, t;
+        divmod(e, rp.T, fr, t);
+        const float2 *v = vis + fr * rp.P * rp.T + t;
+        const float *a = rp.autos + fr * rp.I * rp.T + t;
+        const int I = (int)rp.I, P = (int)rp.P;
+        double m = 1.0;
+        int i = 0, j = 0;
+#pragma unroll 4
+        for (int p = 0; p < P; ++p) {
+            if (rp.prod_map) {
+                i = rp.prod_map[2 * p];
+                j = rp.prod_map[2 * p + 1];
+            }
+            if (i != j) {
+                const float2 x = v[p * rp.T];
+                const double ab = (double)a[i * rp.T] * (double)a[j * rp.T];
+                const double term = 1.0 - ((double)x.x * (double)x.x + (double)x.y * (double)x.y) / ab;
+                // a NaN term never wins
+                if (ab > 0.0 && ab != __builtin_inf() && term < m) m = term;
+            }
+            if (++j == I) j = ++i;
+        }
+        scale[e] = m;
+    }
+}
+
 __global__ __launch_bounds__(256) void k_ones(double *__restrict__ out, int64_t n)
 {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
@@ -321,13 +359,24 @@ hipError_t launch_noise_comp(const float *vis, const RoundParams &rp, double *sc
 {
     const int64_t n = rp.F * rp.T;
     if (n == 0) return hipSuccess;
+    const float2 *v = reinterpret_cast<const float2 *>(vis);
+    // A thread per sample up to 6 inputs, and up to 9 where the samples fill the
+    // card (105 MB of 8 inputs, 1 time: 114 us there, 1077 below; 1 MB of 1 time:
+    // 10 and 8).
+    if (rp.P <= 21 || (rp.P <= 45 && n >= 131072)) {
+        hipLaunchKernelGGL(k_noise_comp_small, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1 << 22)),
+                           dim3(256), 0, s, v, rp, scale, n);
+        return hipGetLastError();
+    }
     const bool lds = rp.I <= kCompAutos;
-    const int64_t fit = lds ? kCompAutos / std::max<int64_t>(rp.I, 1) : kCompThreads;
-    const int Tb = (int)std::min<int64_t>({rp.T, kCompThreads, fit});
+    // (the times in equal tiles: 130 as 65 and 65)
+    const int64_t fit = std::min<int64_t>(lds ? kCompAutos / rp.I : kCompTimes, kCompTimes);
+    const int64_t tiles0 = (rp.T + fit - 1) / fit;
+    const int Tb = (int)((rp.T + tiles0 - 1) / tiles0);
     const int64_t tiles = (rp.T + Tb - 1) / Tb;
     const int64_t most = lds ? kCompPairs : 1 << 28; // products of a workgroup
-    // Enough parts for three workgroups per CU (as many as reside), if each
-    // keeps four steps, and for the table.
+    // Enough parts for three workgroups per CU (as many as reside up to 40 KiB
+    // of table and autos), if each keeps four steps, and for the table.
     const int64_t steps = rp.P / (kCompAhead * (kCompThreads / Tb));
     const int parts = (int)std::max<int64_t>(
         {(rp.P + most - 1) / most, 1,
@@ -342,13 +391,15 @@ hipError_t launch_noise_comp(const float *vis, const RoundParams &rp, double *sc
     const dim3 grid((unsigned)gx, (unsigned)parts, (unsigned)tiles);
     const int64_t per = (rp.P + parts - 1) / parts;
     const size_t dyn = lds ? 4 * (size_t)(per + rp.I * Tb) : 0;
-    const float2 *v = reinterpret_cast<const float2 *>(vis);
-    if (lds)
-        hipLaunchKernelGGL((k_noise_comp<true>), grid, dim3(kCompThreads), dyn, s, v, rp, scale, Tb,
-                           parts);
+    if (!lds)
+        hipLaunchKernelGGL((k_noise_comp<false, kCompThreads>), grid, dim3(kCompThreads), 0, s, v, rp,
+                           scale, Tb, parts);
+    else if (parts == 1 && rp.F * tiles <= 256) // a CU each: more threads, fewer steps
+        hipLaunchKernelGGL((k_noise_comp<true, 2 * kCompThreads>), grid, dim3(2 * kCompThreads), dyn, s,
+                           v, rp, scale, Tb, parts);
     else
-        hipLaunchKernelGGL((k_noise_comp<false>), grid, dim3(kCompThreads), 0, s, v, rp, scale, Tb,
-                           parts);
+        hipLaunchKernelGGL((k_noise_comp<true, kCompThreads>), grid, dim3(kCompThreads), dyn, s, v, rp,
+                           scale, Tb, parts);
     return hipGetLastError();
 }
 

@@ -31,9 +31,8 @@ def host(t):
     return t.cpu().numpy()
 
 
-# T a power of two up to 1024 takes the one-workgroup-per-frequency kernel
-# (including steps of the product index that wrap several rows of inputs:
-# T = 2 with 40 inputs), other T the per-time kernel.
+# Up to 6 inputs a thread takes a sample, above that a workgroup takes one
+# frequency's products (T = 2 with 40 inputs: many rows of products per step).
 CASES = [(4, 8, 64, 0, 0.4), (3, 5, 7, 1, 0.0), (2, 16, 130, 2, 2.0), (1, 1, 5, 3, 0.4),
          (2, 2, 65, 4, 1.0), (5, 3, 1, 5, 0.4), (16, 8, 64, 6, 0.1), (2, 40, 2, 7, 0.4),
          (1, 4, 1024, 8, 0.4), (3, 13, 32, 9, 0.0)]
@@ -151,4 +150,26 @@ def test_compensation_over_the_float32_range(bsg, lo, hi):
     vis = vis.view(np.complex64)[..., 0]
     ref = oracle.noise_compensation(vis, autos)
     got = host(bsg.noise_compensation(dev(vis), dev(autos)))
+    assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
+
+
+@pytest.mark.parametrize("F,I,T,seed", [(30000, 2, 7, 1), (40000, 6, 1, 2), (5000, 6, 64, 3), (1, 7, 3, 4),
+                                        (18725, 7, 7, 5), (18724, 7, 7, 6), (1033, 9, 127, 7), (1008, 9, 130, 8),
+                                        (300, 10, 129, 9), (2, 24, 64, 10), (256, 12, 128, 11),
+                                        (257, 12, 128, 12), (200000, 1, 3, 13), (4400000, 2, 1, 14)])
+def test_compensation_small_arrays(bsg, F, I, T, seed):
+    """Few products over many samples, on both sides of each rule that picks
+    the kernel, its threads and its times."""
+    rng = np.random.default_rng(seed)
+    P = I * (I + 1) // 2
+    autos = rng.uniform(0.5, 2.0, (F, I, T)).astype(np.float32)
+    vis = rng.uniform(-0.4, 0.4, (F, P, T, 2)).astype(np.float32).view(np.complex64)[..., 0]
+    for v in (0.0, -1.0, np.inf, np.nan, 1e-40):
+        autos.reshape(-1)[rng.integers(0, autos.size, max(1, autos.size // 501))] = v
+    pm = np.ascontiguousarray(synth.product_pairs(I)[rng.permutation(P)])
+    ref = oracle.noise_compensation(vis, autos)
+    got = host(bsg.noise_compensation(dev(vis), dev(autos)))
+    assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
+    ref = oracle.noise_compensation(vis, autos, prod_map=pm)
+    got = host(bsg.noise_compensation(dev(vis), dev(autos), prod_map=dev(pm)))
     assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
