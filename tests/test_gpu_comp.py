@@ -173,3 +173,16 @@ def test_compensation_small_arrays(bsg, F, I, T, seed):
     ref = oracle.noise_compensation(vis, autos, prod_map=pm)
     got = host(bsg.noise_compensation(dev(vis), dev(autos), prod_map=dev(pm)))
     assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
+
+
+@pytest.mark.parametrize("I", [16384, 16385])
+def test_compensation_largest_arrays(bsg, I):
+    """The most inputs whose autos have a place in LDS, and one more."""
+    P = I * (I + 1) // 2
+    g = torch.Generator(device="cuda:0").manual_seed(I)
+    v = torch.rand((1, P, 1, 2), generator=g, device="cuda:0") * 0.6 - 0.3
+    a = torch.rand((1, I, 1), generator=g, device="cuda:0") + 0.5
+    vis = torch.view_as_complex(v)
+    ref = oracle.noise_compensation(host(vis), host(a))
+    got = host(bsg.noise_compensation(vis, a))
+    assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
