@@ -1070,8 +1070,11 @@ __device__ __forceinline__ void unstage_block(const uint8_t *lds, int64_t elems,
             unstage_fast<EC>(lds, elems, dst);
             return;
         }
-        if (fast_out) { // a stream's short last block
-            block_inverse_bits(lds, dst, elems, E);
+        if (fast_out) { // no whole number of units
+            constexpr int NC = group_columns<EC>();
+            const int pb = (int)(elems / 8);
+            for (int t = threadIdx.x; t < pb * NC; t += kWave)
+                group_inverse<EC, int>(lds, pb, t / NC, t % NC, dst);
             return;
         }
     }

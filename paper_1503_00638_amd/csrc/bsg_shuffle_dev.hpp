@@ -298,32 +298,53 @@ __device__ __forceinline__ void block_forward_bits(const uint8_t *in, uint8_t *o
     }
 }
 
-// Its inverse, from LDS, for a stream's short last block (a bit per LDS read
-// took 9 us longer for 1844 4-byte elements).
-__device__ __forceinline__ void block_inverse_bits(const uint8_t *in, uint8_t *out, int64_t elems,
-                                                   int64_t E)
+// 8 elements ("group" g) of a block whose elements are no whole number of
+// units, from its planes to `out` (16-byte aligned at the block's start): their
+// bytes 4 c .. 4 c + 3 (all of them for E < 4), as the 8 x 8 bit matrices of
+// byte g of 8 planes per element byte, then whole dwords.  (Stored byte by byte
+// the wavefront's stores fell 8 E bytes apart: 42 MB of 8-byte elements in
+// blocks of 1008 took 200 us to decompress, this 44, a lane per element 78.)
+template <int E> constexpr int group_columns() { return E >= 4 ? E / 4 : 1; }
+
+template <int E, typename Int>
+__device__ __forceinline__ void group_inverse(const uint8_t *planes, Int pb, Int g, int c,
+                                              uint8_t *__restrict__ out)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t pb = elems / 8;
-    const int rows = pb < 64 ? 64 / (int)pb : 1;
-    const int k0 = rows > 1 ? lane / (int)pb : 0, g0 = lane - k0 * (int)pb;
-    if (k0 >= rows) return;
-    for (int64_t k = k0; k < E; k += rows) {
-        for (int64_t g = g0; g < pb; g += 64) {
-            uint32_t b[8];
+    constexpr int KB = E < 4 ? E : 4;
+    const uint8_t *p = planes + 8 * KB * c * pb + g;
+    uint32_t lo[KB], hi[KB];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) b[j] = in[(8 * k + j) * pb + g];
-            uint32_t lo = b[0] | b[1] << 8 | b[2] << 16 | b[3] << 24;
-            uint32_t hi = b[4] | b[5] << 8 | b[6] << 16 | b[7] << 24;
-            transpose8(lo, hi);
+    for (int k = 0; k < KB; ++k) {
+        uint32_t b[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                out[(8 * g + i) * E + k] = (uint8_t)((i < 4 ? lo : hi) >> (8 * (i & 3)));
+        for (int j = 0; j < 8; ++j) b[j] = p[(8 * k + j) * pb];
+        lo[k] = b[0] | b[1] << 8 | b[2] << 16 | b[3] << 24;
+        hi[k] = b[4] | b[5] << 8 | b[6] << 16 | b[7] << 24;
+        transpose8(lo[k], hi[k]);
+    }
+    if constexpr (E == 1) {
+        reinterpret_cast<uint2 *>(out)[g] = make_uint2(lo[0], hi[0]);
+    } else if constexpr (E == 2) {
+        reinterpret_cast<uint4 *>(out)[g] =
+            make_uint4(perm(lo[1], lo[0], 0x05010400u), perm(lo[1], lo[0], 0x07030602u),
+                       perm(hi[1], hi[0], 0x05010400u), perm(hi[1], hi[0], 0x07030602u));
+    } else {
+        uint32_t e[8];
+        byte_transpose4(lo[0], lo[1], lo[2], lo[3], e[0], e[1], e[2], e[3]);
+        byte_transpose4(hi[0], hi[1], hi[2], hi[3], e[4], e[5], e[6], e[7]);
+        if constexpr (E == 4) {
+            uint4 *o = reinterpret_cast<uint4 *>(out) + 2 * g;
+            o[0] = make_uint4(e[0], e[1], e[2], e[3]);
+            o[1] = make_uint4(e[4], e[5], e[6], e[7]);
+        } else {
+            uint32_t *o = reinterpret_cast<uint32_t *>(out) + 8 * g * (E / 4) + c;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o[i * (E / 4)] = e[i];
         }
     }
 }
 
-// And the inverse for many blocks without a register path: a lane per element,
+// The generic inverse: a lane per element,
 // so that a wavefront's byte stores fall into neighbouring lines (with 8
 // elements per lane 2 Mi 6-byte elements took 47 us instead of 37, and their
 // decompression 53 instead of 30).

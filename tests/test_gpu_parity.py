@@ -298,6 +298,47 @@ def test_short_last_blocks(bsg, E):
             assert np.array_equal(host(off), data), last
 
 
+@pytest.mark.parametrize("E", [1, 2, 4, 8, 12, 16])
+def test_blocks_of_part_units(bsg, E):
+    """Full blocks whose elements are no whole number of the transposes' units,
+    from one group of 8 to the largest of each instance block size, aligned and
+    not, with a raw tail: the transpose both ways and the stream, alone and in
+    a batch."""
+    sizes = [8, 24, 40, 136]
+    for top in (4096, 8192, 16384, 65536):
+        k = top // E // 8 * 8
+        sizes.append(k - 8 if k % 128 == 0 else k)
+    datas, streams = [], []
+    for nb in sizes:
+        n = 3 * nb + nb // 16 * 8 + 3
+        data = synth.gen_walk_int16(n * E // 2 + 1, nb + E).view(np.uint8)[: n * E].copy()
+        s = oracle.compress(data, E, nb)
+        ref = oracle.bitshuffle(data, E, nb)
+        for off in (0, 5):
+            buf = torch.zeros(n * E + 16, dtype=torch.uint8, device="cuda:0")
+            x = buf[off:off + n * E]
+            x.copy_(dev(data))
+            assert np.array_equal(host(bsg.compress_sync(x, E, nb)), s), (nb, off)
+            assert np.array_equal(host(bsg.bitshuffle(x, E, nb)), ref), (nb, off)
+            x.zero_()
+            bsg.decompress(dev(s), s.size, n, E, nb, out=x)
+            assert np.array_equal(host(x), data), (nb, off)
+            x.zero_()
+            bsg.bitunshuffle(dev(ref), E, nb, out=x)
+            assert np.array_equal(host(x), data), (nb, off)
+        datas.append(data)
+        streams.append(s)
+    plan = bsg.BatchPlan.for_compress([dev(d) for d in datas], E, sizes)
+    nb = host(plan.compress())
+    for k, s in enumerate(streams):
+        assert nb[k] == s.size and np.array_equal(host(plan.outs[k])[: s.size], s), sizes[k]
+    plan = bsg.BatchPlan.for_decompress([dev(s) for s in streams], [s.size for s in streams],
+                                        [d.size // E for d in datas], E, sizes)
+    assert not host(plan.decompress()).any()
+    for k, d in enumerate(datas):
+        assert np.array_equal(host(plan.outs[k])[: d.size], d), sizes[k]
+
+
 @pytest.mark.parametrize("F,I,T", [(1, 5, 23), (1, 5, 22), (2, 3, 31), (7, 4, 5), (3, 7, 50), (1, 1, 9)])
 def test_fused_short_last_block(bsg, F, I, T):
     """The rounding fused into a last block of no whole number of units."""
