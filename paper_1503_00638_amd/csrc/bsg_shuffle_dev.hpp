@@ -298,14 +298,72 @@ __device__ __forceinline__ void block_forward_bits(const uint8_t *in, uint8_t *o
     }
 }
 
-// 8 elements ("group" g) of a block whose elements are no whole number of
-// units, from its planes to `out` (16-byte aligned at the block's start): their
-// bytes 4 c .. 4 c + 3 (all of them for E < 4), as the 8 x 8 bit matrices of
-// byte g of 8 planes per element byte, then whole dwords.  (Stored byte by byte
-// the wavefront's stores fell 8 E bytes apart: 42 MB of 8-byte elements in
-// blocks of 1008 took 200 us to decompress, this 44, a lane per element 78.)
+// A block whose elements are no whole number of units goes by groups of 8
+// elements and, for E >= 4, columns of 4 of their bytes: byte g of 8 planes is
+// the 8 x 8 bit matrix of one byte of the group's elements.  The elements (from
+// a 16-byte aligned block) are moved as whole dwords, the plane bytes one by one.
 template <int E> constexpr int group_columns() { return E >= 4 ? E / 4 : 1; }
 
+// Column c of group g: the dwords of its elements (2 for E = 1, 4 for E = 2,
+// else one of each of the 8 elements).
+template <int E> constexpr int group_words() { return E == 1 ? 2 : E == 2 ? 4 : 8; }
+
+template <int E, typename Int>
+__device__ __forceinline__ void group_load(const uint8_t *__restrict__ in, Int g, int c,
+                                           uint32_t (&w)[group_words<E>()])
+{
+    if constexpr (E == 1) {
+        const uint2 v = reinterpret_cast<const uint2 *>(in)[g];
+        w[0] = v.x;
+        w[1] = v.y;
+    } else if constexpr (E == 2 || E == 4) {
+#pragma unroll
+        for (int i = 0; i < E / 2; ++i) {
+            const uint4 v = reinterpret_cast<const uint4 *>(in)[(E / 2) * g + i];
+            w[4 * i] = v.x;
+            w[4 * i + 1] = v.y;
+            w[4 * i + 2] = v.z;
+            w[4 * i + 3] = v.w;
+        }
+    } else {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(in) + 8 * g * (E / 4) + c;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = p[i * (E / 4)];
+    }
+}
+
+// Those dwords to byte g of the column's planes.
+template <int E, typename Int>
+__device__ __forceinline__ void group_forward(const uint32_t (&w)[group_words<E>()], Int pb, Int g,
+                                              int c, uint8_t *planes)
+{
+    constexpr int KB = E < 4 ? E : 4;
+    uint32_t lo[KB], hi[KB];
+    if constexpr (E == 1) {
+        lo[0] = w[0];
+        hi[0] = w[1];
+    } else if constexpr (E == 2) {
+        lo[0] = perm(w[1], w[0], 0x06040200u);
+        lo[1] = perm(w[1], w[0], 0x07050301u);
+        hi[0] = perm(w[3], w[2], 0x06040200u);
+        hi[1] = perm(w[3], w[2], 0x07050301u);
+    } else {
+        byte_transpose4(w[0], w[1], w[2], w[3], lo[0], lo[1], lo[2], lo[3]);
+        byte_transpose4(w[4], w[5], w[6], w[7], hi[0], hi[1], hi[2], hi[3]);
+    }
+    uint8_t *p = planes + 8 * KB * c * pb + g;
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+        transpose8(lo[k], hi[k]);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            p[(8 * k + j) * pb] = (uint8_t)((j < 4 ? lo[k] : hi[k]) >> (8 * (j & 3)));
+    }
+}
+
+// And back, from the planes to the elements.  (Stored byte by byte the
+// wavefront's stores fell 8 E bytes apart: 42 MB of 8-byte elements in blocks
+// of 1008 took 200 us to decompress, this 44, a lane per element 78.)
 template <int E, typename Int>
 __device__ __forceinline__ void group_inverse(const uint8_t *planes, Int pb, Int g, int c,
                                               uint8_t *__restrict__ out)

@@ -349,6 +349,18 @@ def test_fused_short_last_block(bsg, F, I, T):
         assert np.array_equal(host(out)[: int(nb.item())], ref), B
 
 
+@pytest.mark.parametrize("F,I,T", [(40, 5, 1), (9, 7, 2), (7, 6, 3), (6, 5, 4), (3, 9, 5), (2, 12, 30), (3, 4, 64)])
+def test_fused_blocks_of_part_units(bsg, F, I, T):
+    """The rounding fused into full blocks of no whole number of units: runs of
+    four visibilities over many product rows, two or one."""
+    vis, autos = synth.gen_vis(F, I, T, F + T, N)
+    r = oracle.round_to_noise(vis, autos, N, 0.01)
+    for B in (8, 24, 40, 248, 1000, 2040):
+        ref = oracle.compress(r, 4, B)
+        out, nb = bsg.round_compress(dev(vis), dev(autos), N, 0.01, block_size=B)
+        assert np.array_equal(host(out)[: int(nb.item())], ref), B
+
+
 @pytest.mark.parametrize("lit_max", [1, 3, 9, 40, 300])
 def test_compress_literal_runs(bsg, lit_max):
     """Literal runs of 0 .. lit_max bytes at every alignment (the copies of a
