@@ -33,23 +33,31 @@ __global__ __launch_bounds__(256) void k_shuffle_fast(const uint8_t *__restrict_
     }
 }
 
-// One block whose elements are no whole number of units.
+// Blocks whose elements are no whole number of units, a thread per group and
+// column.  Bound by the plane side's byte accesses: 42 MB in 21 us for 2- and
+// 4-byte elements (4.0 TB/s), 24 for 1, 38 to 45 for 8 to 16.  A wavefront per
+// block took 80 to 92 us for blocks of 4000 bytes, a thread per unit of one
+// long block 128 bytes at a time.
 template <int E, bool INV>
-__global__ __launch_bounds__(64) void k_shuffle_part(const uint8_t *__restrict__ in,
-                                                     uint8_t *__restrict__ out, int64_t nb)
+__global__ __launch_bounds__(256) void k_shuffle_groups(const uint8_t *__restrict__ in,
+                                                        uint8_t *__restrict__ out, int64_t nblocks,
+                                                        int64_t nb)
 {
-    const int64_t u = int64_t(blockIdx.x) * 64 + threadIdx.x, left = nb - u * Unit<E>::G;
-    if (left <= 0) return;
-    const int c = blockIdx.y; // 4-byte column of the elements
-    uint32_t w[32];
-    if constexpr (!INV) {
-        load_column<E>(in + u * (Unit<E>::G * E), left, c, w);
-        column_forward<E>(w);
-        store_plane_bytes<E>(out, nb / 8, u, c, w);
-    } else {
-        load_plane_bytes<E>(in, nb / 8, u, c, w);
-        column_inverse<E>(w);
-        store_column<E>(out + u * (Unit<E>::G * E), left, c, w);
+    constexpr int NC = group_columns<E>();
+    const int64_t pb = nb / 8, per = pb * NC, total = nblocks * per;
+    for (int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x; t < total;
+         t += int64_t(gridDim.x) * 256) {
+        const int64_t blk = total >> 32 == 0 ? (int64_t)((uint32_t)t / (uint32_t)per) : t / per;
+        const int64_t r = t - blk * per, off = blk * nb * E;
+        const int64_t g = r / NC;
+        const int c = (int)(r - g * NC);
+        if constexpr (!INV) {
+            uint32_t w[group_words<E>()];
+            group_load<E, int64_t>(in + off, g, c, w);
+            group_forward<E, int64_t>(w, pb, g, c, out + off);
+        } else {
+            group_inverse<E, int64_t>(in + off, pb, g, c, out + off);
+        }
     }
 }
 
@@ -84,11 +92,13 @@ hipError_t fast_launch(const uint8_t *in, uint8_t *out, int64_t nblocks, int64_t
 }
 
 template <int E, bool INV>
-hipError_t part_launch(const uint8_t *in, uint8_t *out, int64_t nb, hipStream_t s)
+hipError_t groups_launch(const uint8_t *in, uint8_t *out, int64_t nblocks, int64_t nb,
+                         hipStream_t s)
 {
-    const int64_t units = (nb + Unit<E>::G - 1) / Unit<E>::G;
-    hipLaunchKernelGGL((k_shuffle_part<E, INV>), dim3((unsigned)((units + 63) / 64), Unit<E>::NC),
-                       dim3(64), 0, s, in, out, nb);
+    const int64_t total = nblocks * (nb / 8) * group_columns<E>();
+    const int64_t grid = (total + 255) / 256;
+    hipLaunchKernelGGL((k_shuffle_groups<E, INV>), dim3((unsigned)(grid < 1 << 22 ? grid : 1 << 22)),
+                       dim3(256), 0, s, in, out, nblocks, nb);
     return hipGetLastError();
 }
 
@@ -110,14 +120,19 @@ hipError_t blocks_launch(const uint8_t *in, uint8_t *out, int64_t nblocks, int64
         default: break;
         }
     }
-    if (G && aligned && nblocks == 1) {
+    // Else by groups (one-byte elements: blocks and groups start at multiples of
+    // 8); in blocks of fewer than 5 groups of wide elements the plane bytes of a
+    // wavefront's groups lie too far apart (42 MB forward, 16-byte elements:
+    // blocks of 16 51 us in the kernel below, 102 by groups; of 56 84 and 50).
+    const bool few = !INV && E >= 8 && nb < 40 && nb * E >= 96;
+    if (G && !few && (aligned || (E == 1 && ((uintptr_t)in | (uintptr_t)out) % 8 == 0))) {
         switch (E) {
-        case 1: return part_launch<1, INV>(in, out, nb, s);
-        case 2: return part_launch<2, INV>(in, out, nb, s);
-        case 4: return part_launch<4, INV>(in, out, nb, s);
-        case 8: return part_launch<8, INV>(in, out, nb, s);
-        case 12: return part_launch<12, INV>(in, out, nb, s);
-        case 16: return part_launch<16, INV>(in, out, nb, s);
+        case 1: return groups_launch<1, INV>(in, out, nblocks, nb, s);
+        case 2: return groups_launch<2, INV>(in, out, nblocks, nb, s);
+        case 4: return groups_launch<4, INV>(in, out, nblocks, nb, s);
+        case 8: return groups_launch<8, INV>(in, out, nblocks, nb, s);
+        case 12: return groups_launch<12, INV>(in, out, nblocks, nb, s);
+        case 16: return groups_launch<16, INV>(in, out, nblocks, nb, s);
         default: break;
         }
     }

@@ -172,87 +172,6 @@ __device__ __forceinline__ void load_planes(const uint8_t *blk, int64_t plane_by
     }
 }
 
-// A block whose elements are no whole number of units ends in a part of one,
-// and its planes (n_B / 8 bytes) start at any byte: elements past the block's
-// end are left out, and plane bytes are moved one by one (in global memory
-// and in LDS; a stream's short last block, where a ballot per bit of every 64
-// elements took up to 40 us).  Elements of 8 bytes and more go one 4-byte
-// column at a time, so that 32 registers do.
-//
-// Load / store the dwords of column c of a unit with `left` >= 8 elements to
-// the block's end (E <= 4: the unit's only 32 dwords).
-template <int E>
-__device__ __forceinline__ void load_column(const uint8_t *p, int64_t left, int c, uint32_t (&w)[32])
-{
-    constexpr int NC = Unit<E>::NC;
-    const int words = E >= 4 ? (int)(left < 32 ? left : 32)
-                             : (int)(left < Unit<E>::G ? left : Unit<E>::G) * E / 4;
-#pragma unroll
-    for (int k = 0; k < 32; ++k)
-        w[k] = k < words ? reinterpret_cast<const uint32_t *>(p)[k * NC + c] : 0u;
-}
-template <int E>
-__device__ __forceinline__ void store_column(uint8_t *p, int64_t left, int c, const uint32_t (&w)[32])
-{
-    constexpr int NC = Unit<E>::NC;
-    const int words = E >= 4 ? (int)(left < 32 ? left : 32)
-                             : (int)(left < Unit<E>::G ? left : Unit<E>::G) * E / 4;
-#pragma unroll
-    for (int k = 0; k < 32; ++k)
-        if (k < words) reinterpret_cast<uint32_t *>(p)[k * NC + c] = w[k];
-}
-template <int E>
-__device__ __forceinline__ void column_forward(uint32_t (&w)[32])
-{
-    if constexpr (E <= 2)
-        unit_forward<E>(w);
-    else
-        transpose32(w);
-}
-template <int E>
-__device__ __forceinline__ void column_inverse(uint32_t (&w)[32])
-{
-    if constexpr (E <= 2)
-        unit_inverse<E>(w);
-    else
-        transpose32(w);
-}
-// The column's plane bytes of unit u to / from a block laid out as planes.
-template <int E>
-__device__ __forceinline__ void store_plane_bytes(uint8_t *blk, int64_t plane_bytes, int64_t u, int c,
-                                                  const uint32_t (&w)[32])
-{
-    using PW = PlaneWords<E>;
-    constexpr int NPL = E >= 4 ? 32 : PW::NPL;
-    const int64_t left = plane_bytes - u * Unit<E>::PB;
-    uint8_t *dst = blk + 32 * c * plane_bytes + u * Unit<E>::PB;
-#pragma unroll
-    for (int q = 0; q < Unit<E>::PB; ++q) {
-        if (q >= left) break;
-#pragma unroll
-        for (int pl = 0; pl < NPL; ++pl)
-            dst[pl * plane_bytes + q] = (uint8_t)(w[PW::word(pl, q / 4)] >> (8 * (q % 4)));
-    }
-}
-template <int E>
-__device__ __forceinline__ void load_plane_bytes(const uint8_t *blk, int64_t plane_bytes, int64_t u,
-                                                 int c, uint32_t (&w)[32])
-{
-    using PW = PlaneWords<E>;
-    constexpr int NPL = E >= 4 ? 32 : PW::NPL;
-    const int64_t left = plane_bytes - u * Unit<E>::PB;
-    const uint8_t *src = blk + 32 * c * plane_bytes + u * Unit<E>::PB;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) w[k] = 0;
-#pragma unroll
-    for (int q = 0; q < Unit<E>::PB; ++q) {
-        if (q >= left) break;
-#pragma unroll
-        for (int pl = 0; pl < NPL; ++pl)
-            w[PW::word(pl, q / 4)] |= (uint32_t)src[pl * plane_bytes + q] << (8 * (q % 4));
-    }
-}
-
 // 8 x 8 bit transpose: bit j of byte i of (lo, hi) goes to bit i of byte j.
 __device__ __forceinline__ void transpose8(uint32_t &lo, uint32_t &hi)
 {
