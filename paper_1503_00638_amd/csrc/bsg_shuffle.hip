@@ -61,14 +61,14 @@ __global__ __launch_bounds__(256) void k_shuffle_groups(const uint8_t *__restric
     }
 }
 
-template <bool INV>
+template <bool INV, int ROWS>
 __global__ __launch_bounds__(64) void k_shuffle_generic(const uint8_t *__restrict__ in,
                                                         uint8_t *__restrict__ out, int64_t nb,
                                                         int64_t E)
 {
     const int64_t off = int64_t(blockIdx.x) * nb * E;
     if (!INV)
-        block_forward_bits(in + off, out + off, nb, E);
+        block_forward_bits<ROWS>(in + off, out + off, nb, E);
     else
         block_inverse_elements(in + off, out + off, nb, E);
 }
@@ -136,7 +136,18 @@ hipError_t blocks_launch(const uint8_t *in, uint8_t *out, int64_t nblocks, int64
         default: break;
         }
     }
-    hipLaunchKernelGGL((k_shuffle_generic<INV>), dim3((unsigned)nblocks), dim3(64), 0, s, in, out,
+    // Many long blocks of wide elements: 67 MB of 24-byte elements in blocks of
+    // 680 216 us, 139 with 8 bytes at once; 100-byte ones in blocks of 648 923 and
+    // 190.  Few blocks wait for one wavefront's chain instead (2 of 2728 24-byte
+    // elements: 100 and 102 us, 20-byte ones 89 and 119).
+    if constexpr (!INV) {
+        if (E >= 16 && nb >= 128 && nblocks >= 1024) {
+            hipLaunchKernelGGL((k_shuffle_generic<false, 8>), dim3((unsigned)nblocks), dim3(64), 0, s,
+                               in, out, nb, E);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_shuffle_generic<INV, 0>), dim3((unsigned)nblocks), dim3(64), 0, s, in, out,
                        nb, E);
     return hipGetLastError();
 }

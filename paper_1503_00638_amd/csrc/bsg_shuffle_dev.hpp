@@ -193,26 +193,39 @@ __device__ __forceinline__ void transpose8(uint32_t &lo, uint32_t &hi)
 // elements, whose 8 x 8 bits are byte g of the planes 8 k .. 8 k + 7 (several
 // k at once where a block has fewer than 64 such groups).  A ballot per bit
 // of every 64 elements took 48 us for 4 Mi 3-byte elements, this takes 11.
+// ROWS: the bytes k a wavefront's lanes take at once, for elements of 16 bytes
+// and more: its 8 x 8 lanes then read whole pieces of 64 neighbouring elements
+// one after the other instead of the block's length once for every k.  (0: as
+// many as the block leaves lanes for.)
+template <int ROWS = 0>
 __device__ __forceinline__ void block_forward_bits(const uint8_t *in, uint8_t *out, int64_t elems,
                                                    int64_t E)
 {
     const int lane = threadIdx.x & 63;
     const int64_t pb = elems / 8;
-    const int rows = pb < 64 ? 64 / (int)pb : 1;
-    const int k0 = rows > 1 ? lane / (int)pb : 0, g0 = lane - k0 * (int)pb;
-    if (k0 >= rows) return;
-    for (int64_t k = k0; k < E; k += rows) {
+    const auto byte_group = [&](int64_t k, int64_t g) {
+        uint32_t b[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b[i] = in[(8 * g + i) * E + k];
+        uint32_t lo = b[0] | b[1] << 8 | b[2] << 16 | b[3] << 24;
+        uint32_t hi = b[4] | b[5] << 8 | b[6] << 16 | b[7] << 24;
+        transpose8(lo, hi);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            out[(8 * k + j) * pb + g] = (uint8_t)((j < 4 ? lo : hi) >> (8 * (j & 3)));
+    };
+    if constexpr (ROWS > 0) {
+        constexpr int COLS = 64 / ROWS;
+        for (int64_t g = lane % COLS; g < pb; g += COLS)
 #pragma unroll 2
-        for (int64_t g = g0; g < pb; g += 64) {
-            uint32_t b[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) b[i] = in[(8 * g + i) * E + k];
-            uint32_t lo = b[0] | b[1] << 8 | b[2] << 16 | b[3] << 24;
-            uint32_t hi = b[4] | b[5] << 8 | b[6] << 16 | b[7] << 24;
-            transpose8(lo, hi);
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                out[(8 * k + j) * pb + g] = (uint8_t)((j < 4 ? lo : hi) >> (8 * (j & 3)));
+            for (int64_t k = lane / COLS; k < E; k += ROWS) byte_group(k, g);
+    } else {
+        const int rows = pb < 64 ? 64 / (int)pb : 1;
+        const int k0 = rows > 1 ? lane / (int)pb : 0, g0 = lane - k0 * (int)pb;
+        if (k0 >= rows) return;
+        for (int64_t k = k0; k < E; k += rows) {
+#pragma unroll 2
+            for (int64_t g = g0; g < pb; g += 64) byte_group(k, g);
         }
     }
 }

@@ -339,6 +339,21 @@ def test_blocks_of_part_units(bsg, E):
         assert np.array_equal(host(plan.outs[k])[: d.size], d), sizes[k]
 
 
+@pytest.mark.parametrize("E,nb", [(15, 128), (16, 128), (17, 136), (20, 408), (24, 120), (100, 648)])
+@pytest.mark.parametrize("blocks", [1023, 1024, 1025])
+def test_transpose_of_wide_elements(bsg, E, nb, blocks):
+    """Many blocks of elements around and above 16 bytes, at odd addresses (no
+    register path), on both sides of each bound of the wide mapping."""
+    n = blocks * nb + 11
+    data = synth.gen_uniform_bytes(n * E, E + blocks)
+    ref = oracle.bitshuffle(data, E, nb)
+    buf = torch.zeros(n * E + 16, dtype=torch.uint8, device="cuda:0")
+    x = buf[3:3 + n * E]
+    x.copy_(dev(data))
+    assert np.array_equal(host(bsg.bitshuffle(x, E, nb)), ref)
+    assert np.array_equal(host(bsg.bitunshuffle(dev(ref), E, nb)), data)
+
+
 @pytest.mark.parametrize("F,I,T", [(1, 5, 23), (1, 5, 22), (2, 3, 31), (7, 4, 5), (3, 7, 50), (1, 1, 9)])
 def test_fused_short_last_block(bsg, F, I, T):
     """The rounding fused into a last block of no whole number of units."""
