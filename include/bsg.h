@@ -206,12 +206,12 @@ int64_t bsg_compress_workspace_size(int64_t n, int64_t elem_size, int64_t block_
  * workspace: device memory of bsg_compress_workspace_size bytes, 256-byte
  *   aligned; workspace_bytes is its size.  Blocks above 65536 bytes are
  *   rejected (BSG_EINVAL).
- * stream: an input of 16384 blocks or more is encoded in up to 16 segments
- *   on this stream and one of the library's own, while a third stream (also
- *   the library's: both made once per device, default priority) copies each
- *   finished segment's blocks to their place; both are joined back into
- *   this stream, so the call orders like one operation on it, also under
- *   stream capture.  Host threads enqueueing such calls take turns. */
+ * stream: an input of 16384 blocks and 128 MiB or more may be encoded in up to
+ *   16 segments on this stream and one of the library's own, while a third
+ *   stream (also the library's: both made once per device, default priority)
+ *   copies each finished segment's blocks to their place; both are joined
+ *   back into this stream, so the call orders like one operation on it, also
+ *   under stream capture.  Host threads enqueueing such calls take turns. */
 int bsg_compress_lz4(const void *in, void *out, int64_t n, int64_t elem_size,
                      int64_t block_size, int64_t out_capacity, int64_t *d_out_nbytes,
                      void *workspace, int64_t workspace_bytes, void *stream);

@@ -341,7 +341,12 @@ constexpr int64_t kSelfMaxBlocks = 4096;
 
 constexpr int kMaxSeg = 16;             // segments of a large input
 static_assert(kMaxSeg <= kSideEvents, "an event per segment");
-constexpr int64_t kSegMinBlocks = 8192; // ... of at least this many blocks
+// ... of at least this many blocks and bytes: each costs 5 launches and an
+// event on two streams, 14 us where its blocks are small (140,000 blocks of 512
+// bytes, 8-byte elements, 496 us in 16 segments, 300 in one; of 2048 bytes 562 in
+// 16, 478 in 4, 463 in one; of 4096 bytes 708 in 16, 660 in 8, 672 in one).
+constexpr int64_t kSegMinBlocks = 8192;
+constexpr int64_t kSegMinBytes = 64ll << 20;
 // Segments pay only when the encoder leaves registers for the pack waves
 // beside its 4 resident waves per SIMD (LDS allows 16 per CU): at 112 VGPRs
 // or fewer.  An encoder that fills the register file (125 VGPRs for 8-byte
@@ -430,7 +435,8 @@ hipError_t launch_compress(const uint8_t *in, uint8_t *out, const Layout &L, int
     pa.round_tail = rp ? 1 : 0;
 
     // segments of whole tiles
-    int nseg = (int)std::min<int64_t>(kMaxSeg, L.n_blocks / kSegMinBlocks);
+    int nseg = (int)std::min<int64_t>({kMaxSeg, L.n_blocks / kSegMinBlocks,
+                                       L.n_blocks * L.block_bytes() / kSegMinBytes});
     if (nseg > 1 && may_segment) {
         const int regs = for_block_size(
             L.block_bytes(), [&](auto maxb) { return encoder_vgprs_for<maxb.value>(rp, ec); });

@@ -393,9 +393,8 @@ def test_compress_literal_runs(bsg, lit_max):
 
 
 def _segmented_input():
-    # 50,000 blocks of 512 bytes plus a ragged end: three segments of at
-    # least 16,384 blocks, so the encoder runs in segments on two streams
-    # and a third stream packs each finished segment
+    # 50,000 blocks of 512 bytes plus a ragged end: enough blocks for several
+    # segments, too few bytes for more than one
     E, nb = 4, 128
     x = np.concatenate([synth.gen_gauss_int32(nb * 24000, 7, 31),
                         synth.gen_gauss_int32(nb * 26000 + 45, 2, 32)]).view(np.uint8)
@@ -447,6 +446,41 @@ def test_compress_segmented_in_a_graph(bsg):
         torch.cuda.synchronize()
         assert int(nb2.item()) == m, k
         assert torch.equal(out2[:m], eager), k
+        _ = (xd[:4096].float() * 2).sum().item()  # eager work between replays
+
+
+@pytest.mark.parametrize("blocks", [524287, 524288, 786432])
+def test_compress_segments(bsg, blocks):
+    """Blocks of 256 bytes around the size from which the encoder runs in
+    segments on two streams while a third packs each finished one (128 MiB: two
+    segments, 192 MiB: three), with a raw tail: the stream equals the oracle's,
+    eager, one byte short of room, and captured in a graph whose replays have
+    other work and synchronisations between them."""
+    E, nb = 4, 64
+    n = blocks * nb + 5
+    x = np.resize(synth.gen_walk_int16(1 << 20, 3).view(np.uint8), n * E)
+    x[: 1 << 20] = synth.gen_uniform_bytes(1 << 20, 7)
+    ref = oracle.compress(x, E, nb)
+    xd, want = dev(x), dev(ref)
+    m = ref.size
+    out, nbytes = bsg.compress(xd, E, nb)
+    assert int(nbytes.item()) == m and torch.equal(out[:m], want)
+    out.fill_(0xA5)
+    _, nbytes = bsg.compress(xd, E, nb, out=out[:m - 1])
+    assert int(nbytes.item()) == bsg.BSG_ECAPACITY and bool((out[m - 1:] == 0xA5).all())
+    ws = torch.empty(bsg.workspace_size(n, E, nb), dtype=torch.uint8, device="cuda:0")
+    nbytes = torch.zeros(1, dtype=torch.int64, device="cuda:0")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        bsg.compress(xd, E, nb, out=out, workspace=ws, nbytes=nbytes)
+    for k in range(3):
+        out.fill_(k)
+        nbytes.fill_(-7)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert int(nbytes.item()) == m and torch.equal(out[:m], want), k
         _ = (xd[:4096].float() * 2).sum().item()  # eager work between replays
 
 
