@@ -29,18 +29,23 @@ constexpr int64_t kBatchSideMinBlocks = 16384;
 // that its scan and pack run beside the next one's encode.
 constexpr int kMaxParts = 8;
 constexpr int64_t kPartMinBlocks = 8192;
-// An element size of 1, 2, 4 or 8 bytes with at least this many blocks of one
-// instance block size is a class of its own, which its own decoder takes: in
-// 8 KiB blocks the mixed decoder's 128 registers leave 16 workgroups per CU,
-// where those for 1, 2 and 4 bytes (95) have the 18 that LDS allows and the
-// one for 8 takes 109.  Below, the end of one more launch costs more than
+// Elements of 1, 2, 4, 8 bytes and those without a register path ("keys" of one
+// instance block size) share a class where two keys or more have few blocks.  A
+// key of at least kOwnMinBlocks and a single one are classes of their own, which
+// their own decoders take: in 8 KiB blocks the mixed decoder's 128 registers
+// leave 16 workgroups per CU, where those for 1, 2 and 4 bytes (91) and for no
+// register path (58) have the 18 that LDS allows and the one for 8 takes 109.
+// With several keys of few blocks the end of one more launch costs more than
 // that gives.
 // 37 GiB in 4096 chunks of 2, 4 and 8 bytes (1.5 M blocks and more each):
 // decompress 33.6 ms, 34.7 as one mixed class.  0.78 GB in 256 chunks (about
-// 32,000 blocks each): 659 us mixed, 707 in classes of their own.
+// 32,000 blocks each): 659 us mixed, 707 in classes of their own; 8000 blocks,
+// one sixteenth of them of another size: 45 mixed, 56.  100,000 blocks of 4 KiB
+// and 3-byte elements alone: 494 us mixed, 424 in their own class.
 constexpr int64_t kOwnMinBlocks = 65536;
-constexpr int kKeysPerSize = 7; // mixed, 1, 2, 4, 8, 12, 16
-static_assert(kMaxClasses >= kKeysPerSize * 4 + kMaxParts, "classes of a batch");
+constexpr int kKeysPerSize = 8; // mixed, no register path, 1, 2, 4, 8, 12, 16
+// (a mixed class stands for two keys or more)
+static_assert(kMaxClasses >= (kKeysPerSize - 1) * 4 + kMaxParts, "classes of a batch");
 
 struct BatchHeader {
     int32_t count, n_classes;
@@ -66,13 +71,13 @@ struct BatchChunk {
 };
 
 // Element class of a key; place of an element class in it.
-constexpr int kKeyClass[kKeysPerSize] = {kMixed, 1, 2, 4, 8, 12, 16};
+constexpr int kKeyClass[kKeysPerSize] = {kMixed, 0, 1, 2, 4, 8, 12, 16};
 
 int key_of(int ec)
 {
-    for (int i = 1; i < kKeysPerSize; ++i)
-        if (kKeyClass[i] == ec) return i;
-    return 0;
+    int i = 1;
+    while (kKeyClass[i] != ec) ++i;
+    return i;
 }
 
 constexpr int64_t table_bytes(int64_t count)
@@ -389,6 +394,7 @@ hipError_t bdec_dispatch(const uint8_t *t, const BatchClass &C, int wpc, int sch
 {
     return for_block_size(C.maxb, [&](auto maxb) {
         switch (C.ec) {
+        case 0: return launch_bdec<maxb.value, 0>(t, C, wpc, sched, status, s);
         case 1: return launch_bdec<maxb.value, 1>(t, C, wpc, sched, status, s);
         case 2: return launch_bdec<maxb.value, 2>(t, C, wpc, sched, status, s);
         case 4: return launch_bdec<maxb.value, 4>(t, C, wpc, sched, status, s);
@@ -466,8 +472,15 @@ int bsg_batch_build_table(const bsg_chunk *chunks, int32_t count, void *host_tab
                  key_of(element_class(c.elem_size));
         blocks[key[i]] += r.n_blocks;
     }
-    for (int &k : key) // common element sizes with few blocks share a class
-        if (kKeyClass[k % kKeysPerSize] <= 8 && blocks[k] < kOwnMinBlocks) k -= k % kKeysPerSize;
+    // keys of few blocks share a class, two or more of one instance block size
+    const auto few = [&](int k) {
+        return kKeyClass[k % kKeysPerSize] <= 8 && blocks[k] < kOwnMinBlocks;
+    };
+    std::map<int, int> shared; // number of those by size
+    for (const auto &[k, n] : blocks)
+        if (few(k) && n > 0) ++shared[k / kKeysPerSize];
+    for (int &k : key)
+        if (few(k) && shared[k / kKeysPerSize] > 1) k -= k % kKeysPerSize;
     std::vector<int> order(count);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key[a] < key[b]; });

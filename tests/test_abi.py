@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -133,6 +134,50 @@ def test_batch_table_host_calls(L):
     # an unknown block schedule is refused before any device work
     assert L.bsg_batch_compress(buf, vp(4096), vp(256), vp(256), 1 << 30, 0, 2, None) == -1
     assert L.bsg_batch_decompress(buf, vp(4096), vp(256), 0, -1, None) == -1
+
+
+def _batch_classes(L, specs):
+    """(element class, instance block size, chunks, blocks) of every class of
+    the table of a batch of (element size, elements per block, blocks) chunks."""
+    from paper_1503_00638_amd import _lib
+    arr = (_lib.Chunk * len(specs))()
+    for k, (E, nb, blocks) in enumerate(specs):
+        arr[k] = _lib.Chunk(4096, 0, 4096, 0, nb * blocks, E, nb)
+    size = L.bsg_batch_table_bytes(len(specs))
+    table = (ctypes.c_uint8 * size)()
+    assert L.bsg_batch_build_table(arr, len(specs), ctypes.byref(table), size) == 0
+    head = np.frombuffer(table, dtype=np.int32, count=2)
+    assert head[0] == len(specs)
+    rec = np.dtype([("ec", "<i4"), ("maxb", "<i4"), ("first_chunk", "<i4"), ("n_chunks", "<i4"),
+                    ("first_block", "<i8"), ("n_blocks", "<i8")])
+    cls = np.frombuffer(table, dtype=rec, count=head[1], offset=24)
+    return [tuple(int(c[f]) for f in ("ec", "maxb", "n_chunks", "n_blocks")) for c in cls]
+
+
+MIXED = -2
+
+
+@pytest.mark.parametrize("E,ec", [(1, 1), (2, 2), (4, 4), (8, 8), (3, 0), (12, 12), (16, 16)])
+def test_batch_of_one_element_size_has_its_own_class(L, E, ec):
+    """Chunks of one element size have nothing to share a launch with, so they
+    go to the class of that size whatever their number."""
+    nb = 4096 // E // 8 * 8
+    assert _batch_classes(L, [(E, nb, 100), (E, nb, 50)]) == [(ec, 4096, 2, 150)]
+
+
+def test_batch_classes(L):
+    """Two keys or more of few blocks share a class, one of 65,536 blocks does
+    not; other block sizes and 12- and 16-byte elements stay apart, and a chunk
+    without a block is no company."""
+    assert _batch_classes(L, [(4, 512, 100), (8, 256, 1)]) == [(MIXED, 4096, 2, 101)]
+    assert _batch_classes(L, [(4, 512, 100), (3, 512, 1)]) == [(MIXED, 4096, 2, 101)]
+    assert _batch_classes(L, [(3, 512, 100), (6, 512, 10)]) == [(0, 4096, 2, 110)]
+    assert _batch_classes(L, [(4, 512, 100), (8, 1024, 100), (4, 512, 0), (12, 128, 9)]) == \
+        [(4, 4096, 2, 100), (12, 4096, 1, 9), (8, 8192, 1, 100)]
+    assert [c[0] for c in _batch_classes(L, [(4, 512, 100), (8, 256, 0)])] == [4, 8]
+    big = 65536
+    assert [c[0] for c in _batch_classes(L, [(4, 8, big), (8, 8, big - 1), (2, 8, 1)])][-1] == 4
+    assert [c[0] for c in _batch_classes(L, [(4, 8, big), (8, 8, big - 1)])] == [4, 8]
 
 
 def _gfx950_kernel_metadata(lib_path, tmp_path):

@@ -138,6 +138,27 @@ def test_batch_own_class(bsg, E, extra):
         assert np.array_equal(host(dplan.outs[k])[: d.size], d), k
 
 
+@pytest.mark.parametrize("Es", [(1,), (2,), (3,), (3, 6, 7), (4,), (8,), (12,), (16,)])
+def test_batch_of_one_class(bsg, Es):
+    """Chunks of one element size, or all without a register path, in blocks of
+    every instance size with short last blocks and tails: the decoder of that
+    element class in a batch of its own."""
+    specs = [(E, max(b // E // 8 * 8, 8), max(b // E // 8 * 8, 8) * m + 8 * k + 3)
+             for E in Es for k, (b, m) in enumerate([(2000, 5), (4096, 3), (8192, 3), (16384, 2), (65536, 1)])]
+    data = [chunk_data(k, E, n) for k, (E, _, n) in enumerate(specs)]
+    Bs, ns = [b for _, b, _ in specs], [n for _, _, n in specs]
+    Ex = [E for E, _, _ in specs]
+    refs = [oracle.compress(d, E, b) for d, E, b in zip(data, Ex, Bs)]
+    plan = bsg.BatchPlan.for_compress([to_dev(d) for d in data], Ex, Bs)
+    nb = host(plan.compress())
+    for k, ref in enumerate(refs):
+        assert nb[k] == ref.size and np.array_equal(host(plan.outs[k])[: ref.size], ref), specs[k]
+    dplan = bsg.BatchPlan.for_decompress([dev(r) for r in refs], [r.size for r in refs], ns, Ex, Bs)
+    assert not host(dplan.decompress()).any()
+    for k, d in enumerate(data):
+        assert np.array_equal(host(dplan.outs[k])[: d.size], d), specs[k]
+
+
 def test_batch_launch_shape_does_not_change_bytes(bsg):
     data, Es, Bs = mixed()
     xs = [to_dev(d) for d in data]
