@@ -178,11 +178,12 @@ __global__ __launch_bounds__(64) void k_batch_encode(const uint8_t *__restrict__
 }
 
 // As dec_waves_per_eu, but 4 for 4 KiB blocks of 8-byte elements, whose
-// registers beside the block walk's do not fit 5 without spills.
+// registers beside the block walk's do not fit 5 without spills, and 3 for
+// 16-byte elements (one register more, 169, leaves 2: 100,000 blocks 766 us, 975).
 template <int MAXB, int EC> constexpr int bdec_waves_per_eu()
 {
     constexpr int n = dec_waves_per_eu<MAXB, EC>();
-    return EC == 8 && n > 4 ? 4 : n;
+    return EC == 16 && MAXB <= kSmallBlock ? 3 : EC == 8 && n > 4 ? 4 : n;
 }
 
 template <int MAXB, int EC>
@@ -353,17 +354,43 @@ int cu_count()
 constexpr int kEncodeWavesPerCu = 64;
 constexpr int kDecodeWavesPerCu = 256;
 
-int64_t persistent_grid(int64_t n_blocks, int waves_per_cu, int preset)
+// The decoders' preset.  Of one element size up to about 100 blocks per CU whole
+// rounds of as many workgroups as reside beat a workgroup per block, whose last
+// ones start late: 8 KiB blocks of 4-byte elements 16,400 blocks 68 us at 16 per
+// CU and 78 at 256, 20,000 82 and 93, 26,000 128 and 124, 100,000 484 and 436; 4
+// KiB ones 32,000 71 us at 20 and 82 at 256, 45,000 109 and 112.  Blocks without
+// a register path differ more in time (8 KiB: 10,000 109 and 114, 13,000 145 and
+// 138; 4 KiB: 256 at every count), as do those of a mixed class (8000 of 4 and 3
+// bytes 99 and 79).  The 168 registers of 16-byte elements leave 12 (100,000
+// blocks 734 us at 12, 766 at 256).
+int decode_waves(const BatchClass &C, int cus)
 {
-    const int64_t g = (int64_t)cu_count() * (waves_per_cu > 0 ? waves_per_cu : preset);
-    return n_blocks < g ? n_blocks : g;
+    const int64_t per_cu = C.n_blocks / cus;
+    switch (C.maxb <= kSmallBlock ? C.ec : kMixed) {
+    case 0: return C.maxb == kSmallBlock && per_cu < 48 ? 16 : kDecodeWavesPerCu;
+    case 1:
+    case 2:
+    case 4:
+        if (C.maxb == kTinyBlock) return per_cu < 144 ? 20 : kDecodeWavesPerCu;
+        [[fallthrough]];
+    case 8: return per_cu < 96 ? 16 : kDecodeWavesPerCu;
+    case 16: return 12;
+    default: return kDecodeWavesPerCu;
+    }
+}
+
+// The caller's workgroups per CU or the preset, and no more than blocks.
+unsigned persistent_grid(int64_t n_blocks, int waves_per_cu, int preset, int cus)
+{
+    const int64_t g = (int64_t)cus * (waves_per_cu > 0 ? waves_per_cu : preset);
+    return (unsigned)(n_blocks < g ? n_blocks : g);
 }
 
 template <int MAXB, int EC>
 hipError_t launch_benc(const uint8_t *d_table, const BatchClass &C, int wpc, int sched,
                        uint8_t *slots, int32_t *sizes, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_batch_encode<MAXB, EC>), dim3((unsigned)persistent_grid(C.n_blocks, wpc, kEncodeWavesPerCu)),
+    hipLaunchKernelGGL((k_batch_encode<MAXB, EC>), dim3(persistent_grid(C.n_blocks, wpc, kEncodeWavesPerCu, cu_count())),
                        dim3(kWave), 0, s, d_table, C, slots, sizes, sched);
     return hipGetLastError();
 }
@@ -372,7 +399,9 @@ template <int MAXB, int EC>
 hipError_t launch_bdec(const uint8_t *d_table, const BatchClass &C, int wpc, int sched,
                        int32_t *status, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_batch_decode<MAXB, EC>), dim3((unsigned)persistent_grid(C.n_blocks, wpc, kDecodeWavesPerCu)),
+    const int cus = cu_count();
+    hipLaunchKernelGGL((k_batch_decode<MAXB, EC>),
+                       dim3(persistent_grid(C.n_blocks, wpc, decode_waves(C, cus), cus)),
                        dim3(kWave), 0, s, d_table, C, status, sched);
     return hipGetLastError();
 }
@@ -583,7 +612,7 @@ int bsg_batch_compress(const void *host_table, const void *d_table, int64_t *d_n
                            C.n_blocks, tiles);
         hipLaunchKernelGGL(k_bprefix, dim3(nt), dim3(kWave), 0, ps, sizes, C.first_block, C.n_blocks,
                            c == 0 ? 1 : 0, tiles, prefix);
-        const int64_t grid = persistent_grid(C.n_blocks, waves_per_cu, kDecodeWavesPerCu);
+        const int64_t grid = persistent_grid(C.n_blocks, waves_per_cu, kDecodeWavesPerCu, cu_count());
         hipLaunchKernelGGL(k_batch_pack, dim3((unsigned)(grid + C.n_chunks)), dim3(kWave), 0, ps, t,
                            C, grid, slots, sizes, prefix, d_nbytes);
         if (hipGetLastError() != hipSuccess) return BSG_EHIP;

@@ -159,6 +159,22 @@ def test_batch_of_one_class(bsg, Es):
         assert np.array_equal(host(dplan.outs[k])[: d.size], d), specs[k]
 
 
+@pytest.mark.parametrize("E,B,per_cu", [(1, 64, 144), (4, 16, 144), (8, 8, 96), (3, 8, 48), (16, 8, 13),
+                                        (4, 1032, 96), (3, 1368, 48)])
+def test_batch_decoder_grids(bsg, E, B, per_cu):
+    """Classes on both sides of the block count up to which a decoder's grid is
+    the workgroups that reside (4 KiB and 8 KiB instances)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for blocks in (per_cu * cus - 1, per_cu * cus):
+        ns = [B * 999 + 5, B * (blocks - 999)]
+        data = [chunk_data(k, E, n) for k, n in zip((1, 3), ns)]
+        refs = [oracle.compress(d, E, B) for d in data]
+        dplan = bsg.BatchPlan.for_decompress([dev(r) for r in refs], [r.size for r in refs], ns, E, B)
+        assert not host(dplan.decompress()).any()
+        for k, d in enumerate(data):
+            assert np.array_equal(host(dplan.outs[k])[: d.size], d), (blocks, k)
+
+
 def test_batch_launch_shape_does_not_change_bytes(bsg):
     data, Es, Bs = mixed()
     xs = [to_dev(d) for d in data]
