@@ -25,10 +25,15 @@ namespace {
 constexpr int kMaxClasses = kSideEvents; // (one encode event per class)
 // a batch of at least this many blocks splits its classes over two streams
 constexpr int64_t kBatchSideMinBlocks = 16384;
-// A class ends when it holds this many blocks or an eighth of the batch, so
-// that its scan and pack run beside the next one's encode.
+// In a batch of that many blocks and kPartMinBatch bytes a class ends when it
+// holds kPartMinBlocks and an eighth of the batch and leaves a quarter of that
+// for the next one, so that its scan and pack run beside the next one's encode.
+// (A class more costs 5 launches and a last round that does not fill the card:
+// 10,000 blocks of 8 KiB, 4-byte elements, in two classes 142 us, in one 109;
+// 20,000 of 2 KiB 120 and 81.)
 constexpr int kMaxParts = 8;
 constexpr int64_t kPartMinBlocks = 8192;
+constexpr int64_t kPartMinBatch = 128ll << 20;
 // Elements of 1, 2, 4, 8 bytes and those without a register path ("keys" of one
 // instance block size) share a class where two keys or more have few blocks.  A
 // key of at least kOwnMinBlocks and a single one are classes of their own, which
@@ -519,15 +524,21 @@ int bsg_batch_build_table(const bsg_chunk *chunks, int32_t count, void *host_tab
     BatchClass *cls = reinterpret_cast<BatchClass *>(t + sizeof(BatchHeader));
     BatchChunk *ch = reinterpret_cast<BatchChunk *>(t + sizeof(BatchHeader) +
                                                     kMaxClasses * sizeof(BatchClass));
-    int64_t blk = 0, slot = 0;
+    int64_t blk = 0, slot = 0, all = 0, bytes = 0;
     int nc = 0;
-    int64_t all = 0;
-    for (const BatchChunk &r : rows) all += r.n_blocks;
+    std::map<int, int64_t> left; // blocks of a class key still to come
+    for (int i = 0; i < count; ++i) {
+        all += rows[i].n_blocks;
+        bytes += rows[i].n_blocks * rows[i].nb * rows[i].E;
+        left[key[i]] += rows[i].n_blocks;
+    }
+    const bool split = all >= kBatchSideMinBlocks && bytes >= kPartMinBatch;
     const int64_t part = std::max(kPartMinBlocks, all / kMaxParts + 1);
     for (int k = 0; k < count; ++k) {
         BatchChunk r = rows[order[k]];
         const int kk = key[order[k]];
-        if (k == 0 || kk != key[order[k - 1]] || cls[nc - 1].n_blocks >= part) {
+        if (k == 0 || kk != key[order[k - 1]] ||
+            (split && cls[nc - 1].n_blocks >= part && left[kk] >= part / 4)) {
             BatchClass &C = cls[nc++]; // at most 7 x 4 keys and kMaxParts more
             C.ec = kKeyClass[kk % kKeysPerSize];
             C.maxb = kk / kKeysPerSize;
@@ -540,6 +551,7 @@ int bsg_batch_build_table(const bsg_chunk *chunks, int32_t count, void *host_tab
         r.slot_start = slot;
         blk += r.n_blocks;
         slot += r.n_blocks * r.slot_bytes;
+        left[kk] -= r.n_blocks;
         C.n_blocks = blk - C.first_block;
         ch[k] = r;
     }

@@ -180,6 +180,22 @@ def test_batch_classes(L):
     assert [c[0] for c in _batch_classes(L, [(4, 8, big), (8, 8, big - 1)])] == [4, 8]
 
 
+def test_batch_class_parts(L):
+    """A class is split only in a batch of 16,384 blocks and 128 MiB, after an
+    eighth of it and at least 8192 blocks, where a quarter of that is left."""
+    def blocks(chunks, elems, each=1024):
+        return [c[3] for c in _batch_classes(L, [(4, elems, each)] * chunks)]
+    assert blocks(16, 2048) == [8192, 8192]
+    assert blocks(15, 2048) == [15360]           # blocks
+    assert blocks(16, 1024) == [16384]           # bytes
+    assert blocks(32, 1024) == [8192] * 4
+    assert blocks(17, 2048) == [8192, 9216]      # less than a quarter left
+    assert blocks(18, 2048) == [8192, 8192, 2048]
+    assert blocks(1, 2048, 40000) == [40000]     # a chunk is not split
+    got = blocks(1000, 2048)
+    assert sum(got) == 1024000 and len(got) == 8 and min(got) > 120000
+
+
 def _gfx950_kernel_metadata(lib_path, tmp_path):
     """(kernel name, private segment bytes per lane) of every kernel in the
     library's gfx950 code objects (one offload bundle per source file)."""

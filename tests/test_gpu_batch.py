@@ -115,6 +115,36 @@ def test_batch_split_classes(bsg, blocks):
         assert np.array_equal(host(dplan.outs[k])[: d.size], d), k
 
 
+def test_batch_split_over_streams(bsg):
+    """A batch of 150 MB whose mixed class is split, its parts encoded on two
+    streams and packed on a third, beside classes of their own; one chunk one
+    byte short of its stream."""
+    specs = [(E, 8192 // E // 8 * 8, 8192 // E // 8 * 8 * (1100 + 70 * k) + 8 * k + 5)
+             for k, E in enumerate((1, 2, 4, 8, 3, 1, 2, 4, 8, 5, 12, 2, 16))]
+    rep = [chunk_data(k, E, 65536) for k, (E, _, _) in enumerate(specs)]
+    data = [np.resize(r, n * E) for r, (E, _, n) in zip(rep, specs)]
+    Es, Bs = [E for E, _, _ in specs], [b for _, b, _ in specs]
+    assert sum(d.size for d in data) > 128 << 20
+    refs = [oracle.compress(d, E, b) for d, E, b in zip(data, Es, Bs)]
+    outs = [torch.full((r.size,), 0xA5, dtype=torch.uint8, device="cuda:0") for r in refs]
+    short = 6
+    outs[short] = outs[short][: refs[short].size - 1]
+    plan = bsg.BatchPlan.for_compress([to_dev(d) for d in data], Es, Bs, outs=outs)
+    for rep in range(2):
+        nb = host(plan.compress())
+        for k, ref in enumerate(refs):
+            if k == short:
+                assert nb[k] == bsg.BSG_ECAPACITY and (host(outs[k]) == 0xA5).all()
+            else:
+                assert nb[k] == ref.size and np.array_equal(host(outs[k]), ref), (rep, k)
+                outs[k].fill_(0xA5)
+    streams = [dev(r) for r in refs]
+    dplan = bsg.BatchPlan.for_decompress(streams, [r.size for r in refs], [n for _, _, n in specs], Es, Bs)
+    assert not host(dplan.decompress()).any()
+    for k, d in enumerate(data):
+        assert np.array_equal(host(dplan.outs[k])[: d.size], d), k
+
+
 @pytest.mark.parametrize("E", [1, 2, 4, 8])
 @pytest.mark.parametrize("extra", [-1, 0])
 def test_batch_own_class(bsg, E, extra):
