@@ -261,9 +261,9 @@ int bsg_decompress_lz4(const void *in, int64_t in_nbytes, void *out, int64_t n,
  * A batch is a set of chunks, each compressed into (or decompressed from) a
  * stream of its own, exactly the stream bsg_compress_lz4 makes for that
  * chunk alone.  Chunks are independent units like the blocks inside them,
- * so one persistent kernel per element-size class walks every block of
- * every chunk; the launches neither allocate nor synchronise with the host,
- * so a hipGraph can capture them.
+ * so one persistent kernel per class of chunks (element size and block size)
+ * walks every block of every chunk; the launches neither allocate nor
+ * synchronise with the host, so a hipGraph can capture them.
  *
  * For compression: in = n elements of elem_size bytes (device), out = the
  *   stream buffer (device, 8-byte aligned) of out_capacity bytes; in_nbytes
@@ -298,8 +298,9 @@ int bsg_batch_build_table(const bsg_chunk *chunks, int32_t count, void *host_tab
 int64_t bsg_batch_workspace_size(const void *host_table);
 
 /* Launch shape of the persistent batch kernels (it never changes the
- * output): waves_per_cu = workgroups per compute unit in the grid (<= 0:
- * 16; one wavefront per workgroup, one block at a time); schedule = how the
+ * output): waves_per_cu = workgroups per compute unit in the grid (<= 0: a
+ * number that the library picks from the class, 12 to 256; one wavefront per
+ * workgroup, one block at a time); schedule = how the
  * blocks of a class are dealt to the workgroups: BSG_SCHED_STRIDED, every
  * grid-th block from the workgroup's index, or BSG_SCHED_RANGES, one
  * contiguous range of blocks per workgroup. */
@@ -312,10 +313,12 @@ int64_t bsg_batch_workspace_size(const void *host_table);
  * out holds nothing meaningful; the other chunks are unaffected).
  * workspace: 256-byte aligned, workspace_bytes >= bsg_batch_workspace_size.
  * waves_per_cu, schedule: the launch shape (above).
- * stream: a batch of 16384 blocks or more in two or more element classes
- *   encodes its classes alternately on this stream and on the library's
- *   encode stream, while the library's pack stream scans and packs
- *   each class (the streams of bsg_compress_lz4, joined back into this one).
+ * stream: a batch of 16384 blocks or more in two or more classes encodes
+ *   them alternately on this stream and on the library's encode stream, while
+ *   the library's pack stream scans and packs each class (the streams of
+ *   bsg_compress_lz4, joined back into this one; host threads enqueueing such
+ *   batches take turns).  One of 128 MiB or more splits its larger classes, so
+ *   this holds for chunks of a single element size too.
  * Errors: BSG_EINVAL (NULL pointers, misaligned buffers, unknown schedule),
  *   BSG_ECAPACITY (workspace too small), BSG_EHIP (launch failure). */
 int bsg_batch_compress(const void *host_table, const void *d_table, int64_t *d_nbytes,

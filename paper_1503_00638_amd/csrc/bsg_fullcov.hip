@@ -19,9 +19,10 @@
 // 512 threads) every multiply-subtract paid an LDS read and write and every
 // column two barriers: 7.36 ms for 65,536 samples of 8 inputs (1.56 TFLOP/s)
 // and 16.3 ms for 16,384 of 11.  With them in registers 1.54 and 2.92 ms
-// (7.5 and 6.6 TFLOP/s): vector issue (about 240 multiplies and subtracts
-// per thread against a square root, two divisions and four LDS round trips
-// per column), four waves per SIMD (128 VGPRs) hiding the chain.  The chain
+// (7.5 and 6.6 TFLOP/s): vector issue (per column and thread about 30
+// multiplies and subtracts in the factorisation and 30 in the inverse, against
+// a square root, two divisions and four LDS round trips), four waves per SIMD
+// (128 VGPRs) hiding the chain.  The chain
 // alone, 16 samples in a call: 51 us (8 inputs, 102 before), 128 us (11,
 // 258 before).  The tile count follows the input count because its loops
 // are unrolled: a smaller array does not carry a larger one's tiles.

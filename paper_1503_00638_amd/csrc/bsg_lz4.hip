@@ -329,7 +329,7 @@ int64_t compress_workspace(const Layout &L)
     int64_t ws = L.n_blocks * slot;
     ws = (ws + 255) / 256 * 256 + ((L.n_blocks * 4 + 255) / 256) * 256;
     ws += ((n_tiles * 8 + 255) / 256) * 256;
-    ws += 256; // (spare)
+    ws += 256; // (unused; callers' sizes and the no-allocation limit stay as they were)
     return ws;
 }
 

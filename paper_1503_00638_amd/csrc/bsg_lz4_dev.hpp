@@ -14,10 +14,12 @@ namespace bsg {
 namespace {
 
 
-// Block sizes the kernels have instances for.  The LDS of a workgroup, and so the blocks in flight on a CU, follows the instance (the
-// encoder's 26, 16, 8 and 2; the decoder's 36, 18, 9 and 2): 4 KiB blocks
-// encoded at 89 us in the 8 KiB instance and 83 in their own (65 MB of 8-byte
-// elements), 16 KiB ones ran 2.7 times as long in the 64 KiB instance.
+// Block sizes the kernels have instances for.  The LDS of a workgroup follows
+// the instance and lets a CU hold 26, 16, 8 and 2 encoders, 35, 18, 9 and 2
+// decoders (in 4 KiB blocks registers leave 20 to 28 of both, 12 for 12- and
+// 16-byte elements): 4 KiB blocks encoded at 89 us in the 8 KiB instance and
+// 83 in their own (65 MB of 8-byte elements), 16 KiB ones ran 2.7 times as long
+// in the 64 KiB instance.
 constexpr int kTinyBlock = 4096;
 constexpr int kSmallBlock = 8192;
 constexpr int kMidBlock = 16384;
@@ -205,9 +207,10 @@ constexpr int kByteShuffle = -1;
 
 // Element class of the batched kernels that take blocks of 1-, 2-, 4- and
 // 8-byte elements and of sizes without a register path in one launch: the
-// block's own element size picks its staging (a wave-uniform branch).  Their
-// register needs lie below what LDS lets reside anyway; 12- and 16-byte
-// elements need more and stay apart.
+// block's own element size picks its staging (a wave-uniform branch).  In 8 KiB
+// blocks the encoder's 114 registers leave the 16 workgroups per CU that LDS
+// does, the decoder's 128 leave 16 of 18; 12- and 16-byte elements need more and
+// stay apart.
 constexpr int kMixed = -2;
 
 // Lanes take 4 elements at a time, so every LDS access is one aligned dword
@@ -1210,7 +1213,7 @@ __device__ __forceinline__ int encode_one(const uint8_t *__restrict__ src, int64
 // Waves per SIMD the decoder kernels ask the register allocator for, of
 // element classes up to 8 bytes: 4 (at most 128 VGPRs) for 8 KiB blocks,
 // where LDS lets 18 blocks reside per CU and one more register would cost a
-// quarter of them; 5 for 4 KiB blocks, where LDS lets 36 reside (8-byte
+// quarter of them; 5 for 4 KiB blocks, where LDS lets 35 reside (8-byte
 // elements, 65 MB: 54.2 us at 127 VGPRs, 50.3 at 85, 51.5 at 80 with spills);
 // 1 (no limit) where the transpose of 12- and 16-byte elements needs more
 // registers or LDS already allows only a few blocks.

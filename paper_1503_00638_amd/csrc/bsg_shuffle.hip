@@ -1,6 +1,7 @@
 // Stage 2a: the Bitshuffle bit transpose within blocks (Section 4.2 of
-// Masui et al.), standalone (no LZ4).  One lane per unit on the fast path;
-// one wavefront per block on the generic path.
+// Masui et al.), standalone (no LZ4).  One lane per unit on the fast path, per
+// group of 8 elements in blocks of no whole number of units; one wavefront per
+// block on the generic path.
 #include "bsg_internal.hpp"
 #include "bsg_shuffle_dev.hpp"
 
