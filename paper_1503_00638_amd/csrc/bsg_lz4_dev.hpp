@@ -13,13 +13,12 @@
 namespace bsg {
 namespace {
 
-
 // Block sizes the kernels have instances for.  The LDS of a workgroup follows
 // the instance and lets a CU hold 26, 16, 8 and 2 encoders, 35, 18, 9 and 2
-// decoders (in 4 KiB blocks registers leave 20 to 28 of both, 12 for 12- and
-// 16-byte elements): 4 KiB blocks encoded at 89 us in the 8 KiB instance and
-// 83 in their own (65 MB of 8-byte elements), 16 KiB ones ran 2.7 times as long
-// in the 64 KiB instance.
+// decoders; registers leave fewer in 4 KiB blocks (20 to 28 and 20 to 32) and
+// of 12- and 16-byte elements (4 to 16).  4 KiB blocks encoded at 89 us in the
+// 8 KiB instance and 83 in their own (65 MB of 8-byte elements), 16 KiB ones
+// ran 2.7 times as long in the 64 KiB instance.
 constexpr int kTinyBlock = 4096;
 constexpr int kSmallBlock = 8192;
 constexpr int kMidBlock = 16384;

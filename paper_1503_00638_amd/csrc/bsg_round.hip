@@ -289,7 +289,7 @@ __global__ __launch_bounds__(THREADS) void k_noise_comp(const float2 *__restrict
 // Small arrays: a thread takes one (frequency, time) and walks its products.
 // A workgroup of the kernel above spends five barriers on each frequency,
 // which 1 to 36 products do not fill: 1,000,000 frequencies of 2 inputs and 7
-// times took 2750 us there, 30 here (HBM).
+// times took 2770 us there, 42 here (280 MB: HBM and the cache before it).
 __global__ __launch_bounds__(256) void k_noise_comp_small(const float2 *__restrict__ vis,
                                                           RoundParams rp,
                                                           double *__restrict__ scale, int64_t n)
